@@ -526,6 +526,7 @@ int gspn_scan_bwd(const void* dy, const void* x, const void* w, const void* lam,
       r.slot_t2b = slot[0]; r.slot_b2t = slot[1];
       r.h_t2b = hv[0]; r.h_b2t = hv[1];
       r.gsum = gsum;
+      r.g_hi = dx; r.g_lo = dlam;
       r.planes = p.planes; r.H = (int)H; r.W = (int)W;
       r.group = p.gh;
       r.logits = p.logits(); r.renorm = (flags & GSPN_FLAG_EDGE_RENORM) ? 1 : 0;
@@ -537,6 +538,7 @@ int gspn_scan_bwd(const void* dy, const void* x, const void* w, const void* lam,
     GradFinishArgs g{};
     g.x = x; g.lam = lam; g.dy = dy; g.gsum = gsum; g.hsum = hsum; g.hsum2 = hv[0] ? hv[0] : hv[1];
     g.hsum3 = hv[0] ? hv[1] : nullptr;
+    g.gsplit = both_vertical(mask) ? 1 : 0;
     if (keep) {
       // du = dy * sum_d h_d, the sum the forward formed
       g.hsum = kept(k.sum);

@@ -24,6 +24,18 @@ __device__ __forceinline__ uint32_t pack_bf2(float a, float b) {
   return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2_t));
 }
 
+// the bits of two floats as two words of upper halves and lower halves (a in
+// the low half of each), and back: fp32 values kept in a pair of 16-bit maps
+__device__ __forceinline__ void split_f2(float a, float b, uint32_t& hi, uint32_t& lo) {
+  const uint32_t x = __float_as_uint(a), y = __float_as_uint(b);
+  hi = (x >> 16) | (y & 0xffff0000u);
+  lo = (x & 0xffffu) | (y << 16);
+}
+__device__ __forceinline__ void join_f2(uint32_t hi, uint32_t lo, float& a, float& b) {
+  a = __uint_as_float((hi << 16) | (lo & 0xffffu));
+  b = __uint_as_float((hi & 0xffff0000u) | (lo >> 16));
+}
+
 __device__ __forceinline__ float to_f(float v) { return v; }
 __device__ __forceinline__ float to_f(bf16 v) { return (float)v; }
 template <typename T> __device__ __forceinline__ T from_f(float v);

@@ -3,13 +3,9 @@
 // The four directions cannot share one sweep (their dependency orders
 // conflict), so sum_d h_d goes through an fp32 workspace `acc` twice:
 //
-//   pass V  (one launch): a workgroup per plane; half of its waves run
-//           top-to-bottom, the other half bottom-to-top.  A row is spread over
-//           the waves of its direction, each lane owning 32 bytes of
-//           positions; the three-way neighbours come from the adjacent lanes
-//           (DPP) and, at wave edges, from an LDS exchange with one barrier per
-//           row.  Each direction stores h for the rows it reaches first; after
-//           the middle row it adds its h to what the other direction stored.
+//   pass V  (one launch): one workgroup per vertical direction and plane
+//           (gspn_vpass_impl.hpp), each direction's h into its own array, or
+//           straight into y when nothing else is added to it.
 //   pass H  (one launch per block of K columns, K = 128 bytes of a row):
 //           left-to-right and right-to-left.  A workgroup owns a band of rows
 //           plus a halo of K rows on each side that has a neighbouring band
@@ -24,308 +20,26 @@
 //           LDS and is added to acc (first half of the blocks) or combined
 //           into y = u * (acc + h) (second half) with coalesced accesses.
 //
-// Both passes pair opposite directions with the same middle-line rule as the
-// resident kernels, so every addition happens in a fixed order and results
-// are reproducible run to run.
+// Pass H pairs its directions with the same middle-line rule as the resident
+// kernels, so every addition happens in a fixed order and results are
+// reproducible run to run.
 #pragma once
 
 #include "gspn_device.hpp"
 #include "gspn_launch.hpp"
 #include "gspn_resident_impl.hpp"
+#include "gspn_vpass_impl.hpp"
 
 namespace gspn {
 
 template <typename T>
 struct LargeCfg {
   static constexpr int VE = 16 / (int)sizeof(T);   // elements per 16-byte vector
-  static constexpr int NPV = 2 * VE;               // vertical: positions per lane (32 bytes)
-  static constexpr int RV = 2;                     // vertical prefetch depth of the inputs (rows)
-  static constexpr int RA = 2;                     // ... of acc and u in the second half
   static constexpr int KH = 128 / (int)sizeof(T);  // horizontal block: columns per launch
   static constexpr int HV = KH / VE;               // 16-byte vectors per row segment
   static constexpr int HROWS = 512;                // rows (lanes) per horizontal workgroup
-  static constexpr int MAX_WPD = 4;                // vertical: waves per direction
-  static constexpr int MAX_W = MAX_WPD * 64 * NPV; // widest row of the vertical pass
+  static constexpr int MAX_W = 8192 / (int)sizeof(T);  // widest row (8 KB)
 };
-
-// ---------------------------------------------------------------------------
-// pass V
-// ---------------------------------------------------------------------------
-struct LargeVParams {
-  const void* x;
-  const void* lam;
-  const void* w;     // packed [n][3][planes][H][W]
-  const void* u;
-  void* y;
-  float* acc;
-  int64_t planes, npc;
-  int H, W;
-  int slot0, slot1;  // weight slot of top-to-bottom / bottom-to-top, -1 when absent
-  int final_out;     // nonzero: write y = u * sum; zero: write the fp32 partial sum
-  float* acc_b;      // split: the grid holds both directions as separate workgroups
-                     // (blockIdx / planes), bottom-to-top writing its h here
-  int split;
-  int grp;           // rows per local-GSPN group (H: the global scan)
-  int renorm;        // Eq. 6 logits (LG kernels): normalise over on-line neighbours only
-  int y_pd;          // unmerged outputs: y is (n, B, C, H, W), this direction's map at slot * npc
-};
-
-// Layout of a row over a wave: the wave's span of 64 * NP positions is cut into
-// NQ chunks of 64 * G positions; lane l holds positions [l G, l G + G) of every
-// chunk.  Each load or store instruction then covers one chunk: consecutive
-// lanes, consecutive addresses, whole cache lines (bf16 and fp32 alike).  The
-// left neighbour of a chunk's first position is lane 63's last one of the
-// previous chunk (a lane read), of the previous wave (LDS) or padding.
-//
-// BOTH: both vertical directions are present; FIN: write y (no pass H follows).
-// LG: the weight maps hold Eq. 6 logits, normalised as they are unpacked.
-template <typename T, int WPD, bool BOTH, bool FIN, bool LG>
-__device__ __forceinline__ void large_v_body(const LargeVParams& p) {
-  using C = LargeCfg<T>;
-  constexpr int NP = C::NPV, R = C::RV, RA = C::RA;
-  static_assert(R % RA == 0, "acc ring slots must repeat with the input ring");
-  constexpr int G = 4;           // positions per lane and chunk
-  constexpr int NQ = NP / G;     // chunks per wave span
-  constexpr int SPAN = 64 * G;   // positions per chunk
-  typedef Pack<T, G> PK;
-  __shared__ float edge[2][2 * WPD][2];  // [step parity][wave][first, last position]
-
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  constexpr bool both = BOTH, fin = FIN;
-  const int dir = both ? (wave >= WPD ? 1 : 0) : (p.split ? (blockIdx.x >= p.planes ? 1 : 0) : (p.slot0 >= 0 ? 0 : 1));
-  const int wi = both ? wave - dir * WPD : wave;
-  const int64_t plane = p.split && dir ? blockIdx.x - p.planes : blockIdx.x;
-  float* const accw = p.split && dir ? p.acc_b : p.acc;  // where a single direction's h goes
-  const int H = p.H, W = p.W;
-  // per chunk: position of the lane's first element, whether it is in the row
-  int po[NQ];
-  bool qok[NQ];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q) {
-    const int pos = wi * NQ * SPAN + q * SPAN + lane * G;
-    qok[q] = pos < W;  // W is a multiple of G
-    po[q] = qok[q] ? pos : 0;
-  }
-  const int64_t pb = plane * (int64_t)H * W;
-  const int slot = dir ? p.slot1 : p.slot0;
-  const int odd = both ? (H & 1) : 0;
-  const int nsteps = H + odd;
-  const int sm = both ? H / 2 + odd : nsteps;  // first step of the second half
-  const int delay = dir ? odd : 0;             // bottom-to-top starts a step late for odd H
-
-  for (int i = threadIdx.x; i < 2 * 2 * WPD * 2; i += blockDim.x) (&edge[0][0][0])[i] = 0.f;
-  __syncthreads();
-
-  const T* w0 = (const T*)p.w + (int64_t)slot * 3 * p.npc;
-  const T* base[5] = {(const T*)p.x + pb, (const T*)p.lam + pb, w0 + pb, w0 + p.npc + pb,
-                      w0 + 2 * p.npc + pb};
-  const T* ubase = (const T*)p.u + pb;
-  const float* abase = p.acc + pb;
-
-  auto t_of = [&](int s) { return s - delay; };
-  auto line_of = [&](int t) {
-    t = t < 0 ? 0 : (t >= H ? H - 1 : t);
-    return dir ? H - 1 - t : t;
-  };
-
-  PK ring[R][5][NQ];
-  // Keeps the last prefetches "used" after a loop: without a use the compiler
-  // drains every outstanding load at the top of each iteration.
-  auto consume_ring = [&]() __attribute__((always_inline)) {
-#pragma unroll
-    for (int k = 0; k < R; ++k)
-#pragma unroll
-      for (int m = 0; m < 5; ++m)
-#pragma unroll
-        for (int q = 0; q < NQ; ++q)
-#pragma unroll
-          for (int i = 0; i < PK::kWords; ++i) asm volatile("" ::"v"(ring[k][m][q].w[i]));
-  };
-  auto load_main = [&](PK (&sl)[5][NQ], int s) __attribute__((always_inline)) {
-    const int64_t off = (int64_t)line_of(t_of(s)) * W;
-#pragma unroll
-    for (int m = 0; m < 5; ++m)
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) sl[m][q].load(base[m] + off + po[q]);
-  };
-  // second-half (or final single-direction) operands: acc and u of the step's row
-  PK uring[RA][NQ];
-  float aring[RA][NQ][G];
-  auto load_aux = [&](int k, int s) __attribute__((always_inline)) {
-    const int64_t off = (int64_t)line_of(t_of(s)) * W;
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if constexpr (fin) uring[k][q].load(ubase + off + po[q]);
-      if constexpr (both) ldv<G>(abase + off + po[q], aring[k][q]);
-    }
-  };
-
-  float hp[NQ][G];
-#pragma unroll
-  for (int q = 0; q < NQ; ++q)
-#pragma unroll
-    for (int j = 0; j < G; ++j) hp[q][j] = 0.f;
-
-  // one step of the scan; SECOND: combine with the other direction's stored h
-  auto step = [&](auto second_tag, int k, int s) __attribute__((always_inline)) {
-    constexpr bool SECOND = decltype(second_tag)::value;
-    const PK(&v)[5][NQ] = ring[k];  // unpacked at use; the slot is refilled after the step
-    const int t = t_of(s);
-    const bool act = t >= 0 && t < H;
-    const int par = s & 1;
-    // local GSPN: the first row of a group starts from a zero state (uniform per direction)
-    const bool rst = act && group_start(line_of(t), p.grp, dir != 0);
-    if (rst) {
-#pragma unroll
-      for (int q = 0; q < NQ; ++q)
-#pragma unroll
-        for (int j = 0; j < G; ++j) hp[q][j] = 0.f;
-    }
-    // neighbours of each chunk's first and last position on the previous row
-    float el[NQ], er[NQ];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      el[q] = from_prev_lane(hp[q][G - 1]);
-      er[q] = from_next_lane(hp[q][0]);
-    }
-    float wl = 0.f, wr = 0.f;  // across waves
-    if constexpr (WPD > 1) {
-      const float nl = edge[par ^ 1][wi > 0 ? wave - 1 : wave][1];
-      const float nr = edge[par ^ 1][wi < WPD - 1 ? wave + 1 : wave][0];
-      wl = (wi > 0 && !rst) ? nl : 0.f;
-      wr = (wi < WPD - 1 && !rst) ? nr : 0.f;
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const float pl = q > 0 ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                                              __builtin_bit_cast(int, hp[q - 1][G - 1]), 63))
-                             : wl;
-      const float nr = q < NQ - 1 ? __builtin_bit_cast(float, __builtin_amdgcn_readlane(
-                                                                   __builtin_bit_cast(int, hp[q + 1][0]), 0))
-                                  : wr;
-      if (lane == 0) el[q] = pl;
-      if (lane == 63) er[q] = nr;
-    }
-    float h[NQ][G];
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      const bool ok = qok[q] && act;
-#pragma unroll
-      for (int j = 0; j < G; ++j) {
-        const float hl = j == 0 ? el[q] : hp[q][j - 1];
-        const float hr = j == G - 1 ? er[q] : hp[q][j + 1];
-        float wa = v[2][q].get(j), wb = v[3][q].get(j), wc = v[4][q].get(j);
-        if constexpr (LG) {
-          const Norm3 nr = normalize3(wa, wb, wc, po[q] + j == 0, po[q] + j == W - 1, p.renorm != 0);
-          wa = nr.w[0];
-          wb = nr.w[1];
-          wc = nr.w[2];
-        }
-        float r = v[1][q].get(j) * v[0][q].get(j);
-        r = fmaf(wa, hl, r);
-        r = fmaf(wb, hp[q][j], r);
-        r = fmaf(wc, hr, r);
-        h[q][j] = ok ? r : 0.f;
-      }
-    }
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int j = 0; j < G; ++j) hp[q][j] = h[q][j];
-    // the new h is materialised before anything below, so the refills of the
-    // ring slots land in the registers just consumed and no loop-carried copy
-    // (which would wait for the loads) is needed
-#pragma unroll
-    for (int q = 0; q < NQ; ++q)
-#pragma unroll
-      for (int j = 0; j < G; ++j) asm volatile("" : "+v"(hp[q][j]));
-    if (lane == 0) edge[par][wave][0] = hp[0][0];
-    if (lane == 63) edge[par][wave][1] = hp[NQ - 1][G - 1];
-    if (act) {
-      const int64_t off = (int64_t)line_of(t) * W;
-#pragma unroll
-      for (int q = 0; q < NQ; ++q) {
-        if (!qok[q]) continue;
-        if constexpr (SECOND) {
-          const int ka = k % RA;
-          float o[G];
-#pragma unroll
-          for (int j = 0; j < G; ++j) o[j] = (both ? aring[ka][q][j] : 0.f) + hp[q][j];
-          if constexpr (fin) {
-#pragma unroll
-            for (int j = 0; j < G; ++j) o[j] *= uring[ka][q].get(j);
-            stv<G>((T*)p.y + (p.y_pd ? (int64_t)slot * p.npc : 0) + pb + off + po[q], o);
-          } else {
-            stv<G>(p.acc + pb + off + po[q], o);
-          }
-        } else {
-          stv<G>(accw + pb + off + po[q], hp[q]);
-        }
-      }
-    }
-    // refills come after the stores, which they may alias, so they stay here
-    asm volatile("" ::: "memory");
-    load_main(ring[k], s + R);
-    if constexpr (SECOND) load_aux(k % RA, s + RA);
-    lds_barrier();
-  };
-
-  // Steps [.., s1) store h (the first half of a pair, or a single direction
-  // that feeds pass H); steps [s1, nsteps) combine with the stored sum.  Idle
-  // steps before step 0 and after the last one align both loops to the ring,
-  // so every load is unconditional and stays in flight across steps.
-  constexpr bool single_final = !both && fin;
-  const int s1 = single_final ? 0 : sm;
-  const int o = (R - s1 % R) % R;
-#pragma unroll
-  for (int k = 0; k < R; ++k) load_main(ring[k], k - o);
-  for (int s0 = -o; s0 < s1; s0 += R) {
-#pragma unroll
-    for (int k = 0; k < R; ++k) step(std::false_type{}, k, s0 + k);
-  }
-  if (s1 >= nsteps) {
-    consume_ring();
-    return;
-  }
-  // the other direction's stores of the first half must be visible
-  __syncthreads();
-#pragma unroll
-  for (int k = 0; k < RA; ++k) load_aux(k, s1 + k);
-  // the first turn of the ring is peeled so that the loop is entered with the
-  // loads in flight in the same order as in its steady state (otherwise the
-  // waits at its top follow the order of the preloads and drain the ring)
-#pragma unroll
-  for (int k = 0; k < R; ++k) step(std::true_type{}, k, s1 + k);
-  for (int s0 = s1 + R; s0 < nsteps; s0 += R) {
-#pragma unroll
-    for (int k = 0; k < R; ++k) step(std::true_type{}, k, s0 + k);
-  }
-  consume_ring();
-#pragma unroll
-  for (int k = 0; k < RA; ++k)
-#pragma unroll
-    for (int q = 0; q < NQ; ++q) {
-      if constexpr (both) {
-#pragma unroll
-        for (int j = 0; j < G; ++j) asm volatile("" ::"v"(aring[k][q][j]));
-      }
-      if constexpr (fin) {
-#pragma unroll
-        for (int i = 0; i < PK::kWords; ++i) asm volatile("" ::"v"(uring[k][q].w[i]));
-      }
-    }
-}
-
-template <typename T, int WPD, bool BOTH, bool FIN, bool LG>
-__global__ void __launch_bounds__(128 * WPD, 2) large_v_kernel(LargeVParams p) {
-  large_v_body<T, WPD, BOTH, FIN, LG>(p);
-}
-// the same pass as the backward's recompute of the vertical directions' h
-// (its own name in kernel traces and counter profiles)
-template <typename T, int WPD, bool BOTH, bool FIN, bool LG>
-__global__ void __launch_bounds__(128 * WPD, 2) large_vrec_kernel(LargeVParams p) {
-  large_v_body<T, WPD, BOTH, FIN, LG>(p);
-}
 
 // ---------------------------------------------------------------------------
 // pass H
@@ -609,7 +323,6 @@ inline bool large_fwd_supported(int H, int W) {
 
 template <typename T>
 struct LargeGeom {
-  int wpd;        // vertical: waves per direction (power of two)
   // horizontal bands (forward, recompute and adjoint): the first and last keep
   // hb_edge rows (one halo of `halo` rows), the others hb_mid (two halos)
   int hb_n, hb_mid, hb_edge, hb_nw, halo;
@@ -621,9 +334,6 @@ template <typename T>
 inline LargeGeom<T> large_geom(int H, int W) {
   using C = LargeCfg<T>;
   LargeGeom<T> g{};
-  const int need = (W + 64 * C::NPV - 1) / (64 * C::NPV);
-  g.wpd = 1;
-  while (g.wpd < need) g.wpd *= 2;
   if (H <= C::HROWS) {
     g.hb_n = 1;
     g.hb_mid = g.hb_edge = H;
@@ -639,25 +349,6 @@ inline LargeGeom<T> large_geom(int H, int W) {
   g.nblk = (W + C::KH - 1) / C::KH;
   g.lds_hb = ((size_t)g.hb_edge * (C::KH + 1) + 4 * (8 + 2) + 64) * sizeof(float);  // h, edges, dummy slots
   return g;
-}
-
-template <typename T, int WPD, bool BOTH, bool FIN>
-hipError_t launch_large_v_mode(const LargeVParams& p, bool rec, bool lg, hipStream_t st) {
-  auto kern = lg ? (rec ? large_vrec_kernel<T, WPD, BOTH, FIN, true> : large_v_kernel<T, WPD, BOTH, FIN, true>)
-                 : (rec ? large_vrec_kernel<T, WPD, BOTH, FIN, false> : large_v_kernel<T, WPD, BOTH, FIN, false>);
-  hipLaunchKernelGGL(kern, dim3((unsigned)(p.planes * (p.split ? 2 : 1))), dim3((BOTH ? 128 : 64) * WPD), 0, st,
-                     p);
-  return hipGetLastError();
-}
-
-// rec: the backward's recompute (same kernel under its own name); lg: the
-// weight maps hold Eq. 6 logits
-template <typename T, int WPD>
-hipError_t launch_large_v(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg) {
-  if (both) return p.final_out ? launch_large_v_mode<T, WPD, true, true>(p, rec, lg, st)
-                               : launch_large_v_mode<T, WPD, true, false>(p, rec, lg, st);
-  return p.final_out ? launch_large_v_mode<T, WPD, false, true>(p, rec, lg, st)
-                     : launch_large_v_mode<T, WPD, false, false>(p, rec, lg, st);
 }
 
 template <typename T, int NW>
@@ -699,32 +390,33 @@ hipError_t large_fwd_t(const LargeFwdArgs& a) {
   const bool has_v = slot[0] >= 0 || slot[1] >= 0, has_h = slot[2] >= 0 || slot[3] >= 0;
 
   if (has_v) {
-    LargeVParams v{};
-    v.x = a.x; v.lam = a.lam; v.w = a.w; v.u = a.u; v.y = a.y; v.acc = a.acc;
+    VScanParams v{};
+    v.x = a.x; v.lam = a.lam; v.w = a.w; v.u = a.u; v.y = a.y;
     v.planes = a.planes; v.npc = npc; v.H = a.H; v.W = a.W;
-    v.slot0 = slot[0]; v.slot1 = slot[1];
-    v.final_out = has_h ? 0 : 1;
-    // both vertical directions feeding a horizontal pass: twice the workgroups,
-    // one direction each, each with its own partial sum (no midpoint pairing,
-    // so the grid has no partly filled last round of whole planes)
+    v.slot[0] = slot[0]; v.slot[1] = slot[1];
     v.grp = (a.group_h > 0 && a.group_h < a.H) ? a.group_h : a.H;
-    v.split = slot[0] >= 0 && slot[1] >= 0 && has_h && a.acc_b != nullptr;
     v.renorm = a.renorm;
-    if (a.y_pd) {
-      // unmerged outputs: every direction writes its own y, nothing is summed
-      v.final_out = 1;
-      v.split = slot[0] >= 0 && slot[1] >= 0;
-      v.y_pd = 1;
-    }
-    v.acc_b = a.acc_b;
-    if (v.split && 2 * a.planes > 0x7fffffffLL) return hipErrorInvalidConfiguration;
-    const bool both = slot[0] >= 0 && slot[1] >= 0 && !v.split;
+    v.y_pd = a.y_pd;
+    const bool both = slot[0] >= 0 && slot[1] >= 0, lg = a.logits != 0;
     hipError_t e;
-    switch (g.wpd) {
-      case 1: e = launch_large_v<T, 1>(v, both, st, false, a.logits != 0); break;
-      case 2: e = launch_large_v<T, 2>(v, both, st, false, a.logits != 0); break;
-      case 4: e = launch_large_v<T, 4>(v, both, st, false, a.logits != 0); break;
-      default: e = hipErrorInvalidValue;
+    if (a.y_pd || (!has_h && !both)) {
+      // unmerged outputs, or a single direction: y leaves at once
+      e = launch_vscan<T>(v, 1, lg, st);
+    } else if (has_h) {
+      // the horizontal pass adds the directions' h: one array each
+      v.out[0] = a.acc;
+      v.out[1] = both ? a.acc_b : a.acc;
+      e = launch_vscan<T>(v, 0, lg, st);
+    } else {
+      // the vertical pair alone: the first one's h through acc
+      v.slot[1] = -1;
+      v.out[0] = a.acc;
+      e = launch_vscan<T>(v, 0, lg, st);
+      if (e != hipSuccess) return e;
+      v.slot[0] = -1;
+      v.slot[1] = slot[1];
+      v.acc = a.acc;
+      e = launch_vscan<T>(v, 2, lg, st);
     }
     if (e != hipSuccess) return e;
   }

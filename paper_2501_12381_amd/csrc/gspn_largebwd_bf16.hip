@@ -2,11 +2,10 @@
 #include "gspn_large_bwd_impl.hpp"
 
 namespace gspn {
+extern template hipError_t launch_vscan<bf16>(VScanParams p, int out, bool lg, hipStream_t st);
+extern template hipError_t launch_vadj<bf16>(VAdjParams p, bool lg, hipStream_t st);
 extern template hipError_t launch_large_h<bf16>(const LargeHParams& p, int nw, int64_t grid, size_t lds, bool lg,
                                                hipStream_t st);
-extern template hipError_t launch_large_v<bf16, 1>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
-extern template hipError_t launch_large_v<bf16, 2>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
-extern template hipError_t launch_large_v<bf16, 4>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
 extern template hipError_t launch_large_hadj_nw<bf16, 1>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
                                                            bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj_nw<bf16, 2>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
@@ -23,12 +22,6 @@ extern template hipError_t launch_large_hadj_nw<bf16, 7>(const LargeHAdjParams& 
                                                            bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj_nw<bf16, 8>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
                                                            bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 1, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 1, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 2, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 2, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 4, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<bf16, 4, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj2_nw<bf16, 1>(const LargeHAdjParams& p0, const LargeHAdjParams& p1,
                                                             int64_t grid, size_t lds, bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj2_nw<bf16, 2>(const LargeHAdjParams& p0, const LargeHAdjParams& p1,

@@ -2,11 +2,10 @@
 #include "gspn_large_bwd_impl.hpp"
 
 namespace gspn {
+extern template hipError_t launch_vscan<float>(VScanParams p, int out, bool lg, hipStream_t st);
+extern template hipError_t launch_vadj<float>(VAdjParams p, bool lg, hipStream_t st);
 extern template hipError_t launch_large_h<float>(const LargeHParams& p, int nw, int64_t grid, size_t lds, bool lg,
                                                hipStream_t st);
-extern template hipError_t launch_large_v<float, 1>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
-extern template hipError_t launch_large_v<float, 2>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
-extern template hipError_t launch_large_v<float, 4>(const LargeVParams& p, bool both, hipStream_t st, bool rec, bool lg);
 extern template hipError_t launch_large_hadj_nw<float, 1>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
                                                            bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj_nw<float, 2>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
@@ -23,12 +22,6 @@ extern template hipError_t launch_large_hadj_nw<float, 7>(const LargeHAdjParams&
                                                            bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj_nw<float, 8>(const LargeHAdjParams& p, int dir, int64_t grid, size_t lds,
                                                            bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 1, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 1, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 2, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 2, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 4, true>(const LargeVAdjParams& p, bool lg, hipStream_t st);
-extern template hipError_t launch_large_vadj_mode<float, 4, false>(const LargeVAdjParams& p, bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj2_nw<float, 1>(const LargeHAdjParams& p0, const LargeHAdjParams& p1,
                                                             int64_t grid, size_t lds, bool lg, hipStream_t st);
 extern template hipError_t launch_large_hadj2_nw<float, 2>(const LargeHAdjParams& p0, const LargeHAdjParams& p1,

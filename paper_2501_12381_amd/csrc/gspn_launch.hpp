@@ -77,6 +77,8 @@ struct GradFinishArgs {
   void* dx;
   void* dlam;         // null when dlam was written per direction
   void* du;
+  int gsplit;         // a further part of sum_d g_d stands in dx and dlam (fp32: in dx;
+                      // bf16: upper halves in dx, lower ones in dlam)
   int64_t n;
   int dx_mode;        // 0: dx = lam * gsum; 1: dx = gsum
   int du_mode;        // 0: du = dy * hsum; 1: du = hsum; 2: du written per direction;
@@ -216,7 +218,7 @@ inline hipError_t large_bwd_v_rec(const LargeBwdVArgs& a, int dtype) {
   return dtype == 0 ? large_bwd_v_rec_f32(a) : large_bwd_v_rec_bf16(a);
 }
 // adjoint of the vertical directions for the same backward (after
-// large_bwd_v_rec): dw of both, gsum += g (fixed order)
+// large_bwd_v_rec): dw of both, their g into gsum (and g_hi, g_lo)
 struct LargeBwdVAdjArgs {
   const void* dy;
   const void* u;
@@ -226,6 +228,8 @@ struct LargeBwdVAdjArgs {
   const float* h_t2b;
   const float* h_b2t;
   float* gsum;
+  void* g_hi;          // dx and dlam: with both directions, bottom-to-top's g goes there
+  void* g_lo;          // (the finish's gsplit), so that they run in one launch
   int64_t planes;
   int H, W;
   int group;

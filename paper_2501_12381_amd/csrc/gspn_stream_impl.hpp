@@ -424,23 +424,44 @@ __global__ void __launch_bounds__(1024) stream_adj_kernel(StreamAdjParams p) {
   }
 }
 
+// fp32 values kept in two maps of T (bf16: upper halves, lower halves; fp32: the first map)
+template <int VEC>
+__device__ __forceinline__ void load_split(const float* hi, const float*, float (&v)[VEC]) { ldv<VEC>(hi, v); }
+template <int VEC>
+__device__ __forceinline__ void load_split(const bf16* hi, const bf16* lo, float (&v)[VEC]) {
+  if constexpr (VEC == 1) {
+    v[0] = __uint_as_float(((uint32_t)__builtin_bit_cast(uint16_t, hi[0]) << 16) |
+                           __builtin_bit_cast(uint16_t, lo[0]));
+  } else {
+    static_assert(VEC == 8, "one 16-byte vector of each map");
+    const uint4 h = *reinterpret_cast<const uint4*>(hi), l = *reinterpret_cast<const uint4*>(lo);
+    join_f2(h.x, l.x, v[0], v[1]);
+    join_f2(h.y, l.y, v[2], v[3]);
+    join_f2(h.z, l.z, v[4], v[5]);
+    join_f2(h.w, l.w, v[6], v[7]);
+  }
+}
+
 // dx = lam * gsum (or gsum itself when it already holds sum_d lam_d g_d),
 // dlam = x * gsum (unless written per direction), du = dy * hsum, hsum, or
 // nothing (per-direction du), where hsum may come in up to three fp32 arrays
-// (added in a fixed order).  Flat and elementwise; VEC: 8 elements a thread
+// and a part of gsum in the dx and dlam maps (added in a fixed order).  Flat and elementwise; VEC: 8 elements a thread
 // with 16-byte accesses (every pointer 16-byte aligned, n a multiple of 8).
 template <typename T, int VEC>
 __global__ void __launch_bounds__(256)
 grad_finish_kernel(const T* __restrict__ x, const T* __restrict__ lam, const T* __restrict__ dy,
-                   const float* __restrict__ gsum, const float* __restrict__ hsum,
-                   const float* __restrict__ hsum2, const float* __restrict__ hsum3,
+                   const float* __restrict__ gsum, const float* __restrict__ hsum, const float* __restrict__ hsum2, const float* __restrict__ hsum3,
                    const T* __restrict__ dy2, const T* __restrict__ dy3,
-                   T* __restrict__ dx, T* __restrict__ dlam, T* __restrict__ du, int64_t n,
-                   int dx_mode, int du_mode) {
+                   T* dx, T* dlam, T* __restrict__ du, int64_t n, int dx_mode, int du_mode, int gsplit) {
   const int64_t stride = (int64_t)gridDim.x * blockDim.x * VEC;
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) * VEC; i < n; i += stride) {
     float gs[VEC], hs[VEC], a[VEC], o[VEC];
     ldv<VEC>(gsum + i, gs);
+    if (gsplit) {
+      load_split<VEC>(dx + i, dlam + i, a);
+#pragma unroll
+      for (int q = 0; q < VEC; ++q) gs[q] += a[q];
+    }
     if (dx_mode == 0) {
       ldv<VEC>(lam + i, a);
 #pragma unroll
@@ -659,7 +680,7 @@ hipError_t grad_finish_t(const GradFinishArgs& a) {
   hipLaunchKernelGGL(kern, dim3((unsigned)blocks), dim3(256), 0, (hipStream_t)a.stream,
                      (const T*)a.x, (const T*)a.lam, (const T*)a.dy, a.gsum, a.hsum, a.hsum2, a.hsum3,
                      (const T*)a.dy2, (const T*)a.dy3, (T*)a.dx, (T*)a.dlam, (T*)a.du, n, a.dx_mode,
-                     a.du_mode);
+                     a.du_mode, a.gsplit);
   return hipGetLastError();
 }
 
