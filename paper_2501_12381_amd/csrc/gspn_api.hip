@@ -177,12 +177,25 @@ bool two_pass_fits(const Problem& p, int dtype, bool backward) {
   return gspn::large_fwd_fits((int)p.H, (int)p.W, dtype);
 }
 
+// AUTO only: the generic resident kernels beyond the sizes of the forced
+// resident families.  Quad: unmerged outputs of any plane up to 256 x 256
+// (forward), four states a plane in LDS (backward); pair: the backward of
+// planes whose states fit one axis at a time.
+constexpr int kAlgoQuad = 100, kAlgoPair = 101;
+
 int choose_algo(const Problem& p, int dtype, int algo, bool backward) {
   if (algo == GSPN_ALGO_STREAM) return GSPN_ALGO_STREAM;
   if (algo == GSPN_ALGO_RESIDENT || algo == GSPN_ALGO_RESIDENT_GENERIC)
     return resident_fits(p, dtype, backward) ? algo : -1;
   if (algo == GSPN_ALGO_TWO_PASS) return two_pass_fits(p, dtype, backward) ? algo : -1;
   if (resident_fits(p, dtype, backward)) return GSPN_ALGO_RESIDENT;
+  const int H = (int)p.H, W = (int)p.W;
+  if (backward) {
+    if (gspn::quad_bwd_fits(H, W)) return kAlgoQuad;
+    if (!(p.flags & kPdFlags) && gspn::pair_bwd_fits(H, W)) return kAlgoPair;
+  } else if (p.y_pd() && gspn::quad_fwd_fits(H, W, true)) {
+    return kAlgoQuad;
+  }
   return two_pass_fits(p, dtype, backward) ? GSPN_ALGO_TWO_PASS : GSPN_ALGO_STREAM;
 }
 
@@ -259,6 +272,7 @@ size_t bwd_ws_bytes(const Problem& p, int algo) {
   if (algo == GSPN_ALGO_TWO_PASS)
     return (both_vertical(p.mask) ? 4 : 3) * fb +
            round_up((size_t)gspn::large_bwd_state_floats(p.planes, (int)p.H) * 4, kWsAlign);
+  if (algo == kAlgoPair) return 2 * fb;  // the vertical directions' sums of h and g
   return 0;
 }
 
@@ -287,10 +301,9 @@ size_t gspn_scan_bwd_workspace_bytes(int64_t B, int64_t C, int64_t H, int64_t W,
   if (saves_state(p, choose_algo(p, dtype, algo, false))) return saved_bwd_ws_bytes(p);
   const int a = choose_algo(p, dtype, algo, true);
   if (a < 0) return 0;
-  // AUTO runs the streaming family instead of the resident one when a pointer
-  // is not 16-byte aligned, so its size covers that case too
-  if (algo == GSPN_ALGO_AUTO && (a == GSPN_ALGO_RESIDENT || a == GSPN_ALGO_RESIDENT_GENERIC))
-    return bwd_ws_bytes(p, GSPN_ALGO_STREAM);
+  // AUTO runs another family instead of the resident one when a pointer is not
+  // 16-byte aligned; its size covers that case (and the streaming family) too
+  if (algo == GSPN_ALGO_AUTO && a != GSPN_ALGO_TWO_PASS) return bwd_ws_bytes(p, GSPN_ALGO_STREAM);
   return bwd_ws_bytes(p, a);
 }
 
@@ -323,7 +336,7 @@ int gspn_scan_fwd(const void* x, const void* w, const void* lam, const void* u, 
   st = check_ws(workspace, workspace_bytes, need, {{x, tb}, {w, wb}, {lam, lb}, {u, ub}, {y, yb}});
   if (st != GSPN_OK) return st;
 
-  if (a == GSPN_ALGO_RESIDENT || a == GSPN_ALGO_RESIDENT_GENERIC) {
+  if (a == GSPN_ALGO_RESIDENT || a == GSPN_ALGO_RESIDENT_GENERIC || a == kAlgoQuad) {
     ResidentFwdArgs r{};
     r.x = x; r.lam = lam; r.w = w; r.u = u; r.y = y;
     r.mask = mask; r.planes = p.planes; r.H = (int)H; r.W = (int)W; r.dtype = dtype;
@@ -429,7 +442,11 @@ int gspn_scan_bwd(const void* dy, const void* x, const void* w, const void* lam,
     for (const void* q : {dy, x, w, lam, u, (const void*)dx, (const void*)dw, (const void*)dlam, (const void*)du})
       if ((uintptr_t)q % 16) {
         if (algo != GSPN_ALGO_AUTO) return GSPN_ERR_ALIGN;
-        a = GSPN_ALGO_STREAM;  // the AUTO workspace size includes this case (a kept state is ignored)
+        // the generic kernels need no alignment; else the streaming family (its
+        // workspace is in the AUTO size).  A kept state is ignored.
+        a = GSPN_ALGO_STREAM;
+        if (gspn::quad_bwd_fits((int)H, (int)W)) a = kAlgoQuad;
+        else if (!(flags & kPdFlags) && gspn::pair_bwd_fits((int)H, (int)W)) a = kAlgoPair;
         keep = false;
         break;
       }
@@ -439,7 +456,8 @@ int gspn_scan_bwd(const void* dy, const void* x, const void* w, const void* lam,
                 {{dy, yb}, {x, tb}, {w, wb}, {lam, lb}, {u, ub}, {dx, tb}, {dw, wb}, {dlam, lb}, {du, ub}});
   if (st != GSPN_OK) return st;
 
-  if (a == GSPN_ALGO_RESIDENT || a == GSPN_ALGO_RESIDENT_GENERIC) {
+  const size_t fb = round_up((size_t)p.npc * 4, kWsAlign);
+  if (a == GSPN_ALGO_RESIDENT || a == GSPN_ALGO_RESIDENT_GENERIC || a == kAlgoQuad || a == kAlgoPair) {
     ResidentBwdArgs r{};
     r.dy = dy; r.x = x; r.lam = lam; r.w = w; r.u = u;
     r.dx = dx; r.dw = dw; r.dlam = dlam; r.du = du;
@@ -449,9 +467,10 @@ int gspn_scan_bwd(const void* dy, const void* x, const void* w, const void* lam,
     r.lam_pd = p.lam_pd(); r.u_pd = p.u_pd(); r.y_pd = p.y_pd();
     r.use_staged = a == GSPN_ALGO_RESIDENT;
     r.stream = stream;
+    if (a == kAlgoQuad) return hip_status(quad_bwd(r));
+    if (a == kAlgoPair) return hip_status(pair_bwd(r, (float*)workspace, (float*)((char*)workspace + fb)));
     return hip_status(resident_bwd(r));
   }
-  const size_t fb = round_up((size_t)p.npc * 4, kWsAlign);
   float* hprev = (float*)workspace;
   float* hsum = (float*)((char*)workspace + fb);
   float* gsum = (float*)((char*)workspace + 2 * fb);

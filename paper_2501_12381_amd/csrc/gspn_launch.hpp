@@ -137,6 +137,24 @@ hipError_t resident_bwd_bf16(const ResidentBwdArgs& a);
 inline hipError_t resident_bwd(const ResidentBwdArgs& a) {
   return a.dtype == 0 ? resident_bwd_f32(a) : resident_bwd_bf16(a);
 }
+// ---- generic resident kernels: any size whose sums or states fit LDS, any
+// alignment (gspn_quad*_impl.hpp) ---------------------------------------------
+hipError_t quad_fwd_f32(const ResidentFwdArgs& a);
+hipError_t quad_fwd_bf16(const ResidentFwdArgs& a);
+bool quad_fwd_fits(int H, int W, bool unmerged);
+hipError_t quad_bwd_f32(const ResidentBwdArgs& a);
+hipError_t quad_bwd_bf16(const ResidentBwdArgs& a);
+inline hipError_t quad_bwd(const ResidentBwdArgs& a) { return a.dtype == 0 ? quad_bwd_f32(a) : quad_bwd_bf16(a); }
+bool quad_bwd_fits(int H, int W);
+// one axis at a time; hsum, gsum: B*C*H*W floats each (used with directions on
+// both axes); merged maps only
+hipError_t pair_bwd_f32(const ResidentBwdArgs& a, float* hsum, float* gsum);
+hipError_t pair_bwd_bf16(const ResidentBwdArgs& a, float* hsum, float* gsum);
+inline hipError_t pair_bwd(const ResidentBwdArgs& a, float* hsum, float* gsum) {
+  return a.dtype == 0 ? pair_bwd_f32(a, hsum, gsum) : pair_bwd_bf16(a, hsum, gsum);
+}
+bool pair_bwd_fits(int H, int W);
+
 // narr: accumulator arrays per plane of the forward (the directions present
 // for unmerged outputs, else 1)
 bool resident_fits(int H, int W, int dtype, bool backward, int narr);

@@ -602,6 +602,7 @@ hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
   const bool pd = a.lam_pd || a.u_pd || a.y_pd;
   if (a.u_pd && !a.y_pd) return hipErrorInvalidValue;  // a merged y with per-direction u: streaming family
   Config c;
+  if (a.y_pd && quad_fwd_fits(a.H, a.W, true)) return sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
   if (!config_for(a.H, a.W, sizeof(T), ptrs, 3, &c, a.y_pd ? n : 1)) return hipErrorInvalidValue;
   ResFwdParams p;
   p.x = a.x; p.lam = a.lam; p.w = a.w; p.u = a.u; p.y = a.y;
@@ -644,10 +645,8 @@ hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
       default: return launch_fixed<T, 64>(p, st);
     }
   }
-  if (c.np == 1 && c.seg == 16) return launch_fwd_vl<T, 1, 16, true>(p, c, st);
-  if (c.np == 1 && c.seg == 32) return launch_fwd_vl<T, 1, 32, true>(p, c, st);
-  if (c.np == 1) return launch_fwd_vl<T, 1, 64, true>(p, c, st);
-  if (c.np == 2) return c.vv ? launch_fwd_vl<T, 2, 64, true>(p, c, st) : launch_fwd_vl<T, 2, 64, false>(p, c, st);
+  if (quad_fwd_fits(a.H, a.W, a.y_pd)) return sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
+  // one sum fits LDS, two do not: planes with a side over 128
   return c.vv ? launch_fwd_vl<T, 4, 64, true>(p, c, st) : launch_fwd_vl<T, 4, 64, false>(p, c, st);
 }
 

@@ -1,0 +1,83 @@
+"""Generic resident kernels (any size that fits LDS, any alignment) against the
+oracle at the sizes where their layout changes: rows narrower than a vector,
+planes sharing a wave (lines of at most 15 and 31), lines of 64/65, 112/113
+(half a line and its halo in one wave) and 128/129 positions, rows whose last
+vector overlaps, plane counts that leave a wave partly empty, absent
+directions, groups, and tensors that are only element-aligned."""
+import pytest
+import torch
+
+import oracle as O
+from paper_2501_12381_amd import ops, synth
+from .parity_util import TOL, np64, normwise
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+# (planes, H, W, mask, group_h, group_w, logits)
+CASES = [(5, 3, 3, 15, 0, 0, False), (9, 7, 7, 15, 0, 0, True), (6, 7, 4, 15, 3, 2, False),
+         (5, 14, 14, 15, 0, 0, True), (4, 15, 15, 11, 4, 6, False), (3, 16, 15, 15, 0, 0, False),
+         (3, 31, 30, 13, 0, 0, True), (2, 32, 33, 15, 9, 7, False), (2, 64, 60, 15, 0, 0, True),
+         (2, 65, 64, 15, 0, 0, False), (2, 45, 77, 15, 23, 39, True), (1, 96, 96, 7, 0, 0, False),
+         (1, 112, 113, 15, 0, 0, True), (2, 113, 112, 14, 40, 0, False), (1, 128, 129, 15, 0, 0, False),
+         (1, 129, 136, 15, 17, 50, True), (1, 40, 240, 15, 0, 0, True), (1, 241, 40, 5, 0, 0, False),
+         (1, 20, 250, 15, 0, 0, True), (1, 250, 36, 10, 0, 0, False), (2, 150, 66, 3, 0, 0, True),
+         (2, 66, 150, 12, 0, 0, True), (1, 8, 256, 15, 0, 0, False), (1, 256, 8, 15, 100, 3, True)]
+
+
+def misalign(t):
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    v = buf[1:].view(t.shape)
+    v.copy_(t)
+    return v
+
+
+@pytest.mark.parametrize("shifted", [False, True], ids=["aligned", "shifted"])
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES, ids=lambda c: "x".join(map(str, c)))
+def test_generic_resident(case, dtype, shifted):
+    planes, H, W, mask, gh, gw, logits = case
+    print(f"[generic] {case} {dtype} shifted={shifted}", flush=True)
+    n = bin(mask).count("1")
+    inp = synth.random_general((1, planes, H, W), n, device=DEV, seed=H * 300 + W, dtype=dtype)
+    if shifted:
+        inp = {k: misalign(v) for k, v in inp.items()}
+    opt = dict(group_h=gh, group_w=gw, logits=logits)
+    y = ops.gspn_scan_fwd(inp["x"], inp["w"], inp["lam"], inp["u"], mask, **opt)
+    got = ops.gspn_scan_bwd(inp["dy"], inp["x"], inp["w"], inp["lam"], inp["u"], mask, **opt)
+    torch.cuda.synchronize()
+    a = {k: np64(v) for k, v in inp.items()}
+    ref = (O.scan_fwd(a["x"], a["w"], a["lam"], a["u"], mask, **opt),) + tuple(
+        O.scan_bwd(a["dy"], a["x"], a["w"], a["lam"], a["u"], mask, **opt))
+    for name, g, r in zip(("y", "dx", "dw", "dlam", "du"), (y,) + tuple(got), ref):
+        e = normwise(g, r)
+        assert torch.isfinite(g).all() and e <= TOL[dtype], f"{name}: {e:.3e}"
+    # the additions have a fixed order: a second run agrees bit for bit
+    again = (ops.gspn_scan_fwd(inp["x"], inp["w"], inp["lam"], inp["u"], mask, **opt),) + tuple(
+        ops.gspn_scan_bwd(inp["dy"], inp["x"], inp["w"], inp["lam"], inp["u"], mask, **opt))
+    for g, h in zip((y,) + tuple(got), again):
+        assert torch.equal(g, h)
+
+
+@pytest.mark.parametrize("pd", [(True, False, False), (False, True, True), (True, True, True), (False, False, True)],
+                         ids=lambda p: "".join("LUY"[i] if f else "-" for i, f in enumerate(p)))
+@pytest.mark.parametrize("shape", [(7, 5), (13, 30), (40, 100), (70, 90)], ids=lambda s: f"{s[0]}x{s[1]}")
+def test_generic_resident_per_direction(shape, pd):
+    """Per-direction maps on the generic kernels (three directions, both dtypes)."""
+    H, W = shape
+    mask, n = 0xD, 3
+    for dtype in (torch.float32, torch.bfloat16):
+        base = synth.random_general((1, 3, H, W), n, device=DEV, seed=7, dtype=dtype)
+        many = synth.random_general((n, 3, H, W), n, device=DEV, seed=8, dtype=dtype)
+        pick = lambda k, f: many[k].view(n, 1, 3, H, W) if f else base[k]
+        x, w = base["x"], base["w"]
+        lam, u, dy = pick("lam", pd[0]), pick("u", pd[1]), pick("dy", pd[2])
+        opt = dict(lam_per_dir=pd[0], u_per_dir=pd[1], y_per_dir=pd[2])
+        y = ops.gspn_scan_fwd(x, w, lam, u, mask, **opt)
+        got = ops.gspn_scan_bwd(dy, x, w, lam, u, mask, **opt)
+        torch.cuda.synchronize()
+        a = [np64(t) for t in (dy, x, w, lam, u)]
+        ref = (O.scan_fwd(*a[1:], mask, **opt),) + tuple(O.scan_bwd(*a, mask, **opt))
+        for name, g, r in zip(("y", "dx", "dw", "dlam", "du"), (y,) + tuple(got), ref):
+            e = normwise(g, r)
+            assert e <= TOL[dtype], f"{name}: {e:.3e}"
