@@ -228,6 +228,6 @@ def gspn_copy_calibration(src: torch.Tensor, dst: torch.Tensor) -> None:
     if dst.numel() * dst.element_size() < n:
         raise ValueError("dst is smaller than src")
     with torch.cuda.device(src.device):
-        st = L.gspn_copy_calibration(src.data_ptr(), dst.data_ptr(), n, _stream(src.device))
+        st = L.gspn_copy_calibration(src.data_ptr(), dst.data_ptr(), n, torch.cuda.current_stream().cuda_stream)
     if st != 0:
         raise L.GSPNError(st, "gspn_copy_calibration")
