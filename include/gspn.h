@@ -136,7 +136,11 @@ enum {
  * family's generic forward (unmerged y, per-direction lam, and per-direction
  * u with unmerged y) and by its per-wave backward (square planes of 16, 28,
  * 32, 56 or 64); GSPN_FLAG_Y_PER_DIR alone also by the two-pass family.  AUTO
- * picks among those. */
+ * picks among those, and beyond the forced resident families' sizes among
+ * generic resident kernels that take any alignment: unmerged outputs of any
+ * plane up to 256 x 256, and the backward of planes whose states fit on chip
+ * (per-direction maps: four fp32 arrays of the plane; else two, one axis at a
+ * time, the other axis's sums through the workspace). */
 enum {
   GSPN_ALGO_AUTO = 0,
   GSPN_ALGO_RESIDENT = 1, /* whole plane kept on chip, all directions in one kernel */
@@ -163,7 +167,8 @@ enum {
                             the adjoints on them (see the flag).
                             Needs W * element size a multiple of 16 bytes and at
                             least 128 bytes, W <= 4096 (bf16) or 2048 (f32), and
-                            16-byte aligned tensors (AUTO falls back to streaming). */
+                            16-byte aligned tensors (AUTO falls back to the generic
+                            resident kernels or to streaming). */
 };
 
 /* Bytes of workspace gspn_scan_fwd needs for this problem (0 if none). */
@@ -205,10 +210,11 @@ int gspn_scan_fwd_noalloc(const void* x, const void* w, const void* lam, const v
                           void* stream);
 
 /* Bytes of workspace gspn_scan_bwd needs for this problem (0 if none).  With
- * GSPN_ALGO_AUTO the size covers every pointer alignment: AUTO runs the
- * streaming family, which needs a workspace (never more than the two-pass
- * one), when a tensor the resident or two-pass kernels would read or write as
- * 16-byte vectors is only element-aligned. */
+ * GSPN_ALGO_AUTO the size covers every pointer alignment: AUTO runs a generic
+ * resident kernel or the streaming family, which need a workspace (never more
+ * than the two-pass one), when a tensor the size-specialised resident or the
+ * two-pass kernels would read or write as 16-byte vectors is only
+ * element-aligned. */
 size_t gspn_scan_bwd_workspace_bytes(int64_t B, int64_t C, int64_t H, int64_t W, uint32_t mask,
                                      gspn_dtype dtype, int64_t group_h, int64_t group_w,
                                      uint32_t flags, int algo);

@@ -171,8 +171,7 @@ bool resident_fits(const Problem& p, int dtype, bool backward) {
 bool two_pass_fits(const Problem& p, int dtype, bool backward) {
   if ((p.flags & ~(kEq6Flags | GSPN_FLAG_Y_PER_DIR | GSPN_FLAG_SAVE_STATE)) || (p.grouped() && !kTwoPassGroups))
     return false;
-  // the backward runs its horizontal directions on the two-pass kernels
-  // (their vertical ones on the streaming kernels)
+  // without a horizontal direction the backward has nothing of its own to run
   if (backward && !(p.mask & (DIR_L2R | DIR_R2L))) return false;
   return gspn::large_fwd_fits((int)p.H, (int)p.W, dtype);
 }

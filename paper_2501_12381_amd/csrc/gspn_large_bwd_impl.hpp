@@ -402,7 +402,7 @@ hipError_t large_bwd_h_t(const LargeBwdHArgs& a) {
   using C = LargeCfg<T>;
   constexpr int K = C::KH;
   if (!large_fwd_supported<T>(a.H, a.W)) return hipErrorInvalidValue;
-  const LargeGeom<T> g = large_geom<T>(a.H, a.W);
+  const LargeGeom<T> g = large_geom<T>(a.H, a.W, a.planes);
   hipStream_t st = (hipStream_t)a.stream;
   const int64_t npc = a.planes * (int64_t)a.H * a.W;
   const int64_t grid = (int64_t)g.hb_n * a.planes;
@@ -465,7 +465,7 @@ template <typename T>
 hipError_t large_bwd_h_pair_t(const LargeBwdHArgs& l2r, const LargeBwdHArgs& r2l) {
   if (!large_fwd_supported<T>(l2r.H, l2r.W)) return hipErrorInvalidValue;
   if (!l2r.saved || !r2l.saved || l2r.dir != 0 || r2l.dir != 1) return hipErrorInvalidValue;
-  const LargeGeom<T> g = large_geom<T>(l2r.H, l2r.W);
+  const LargeGeom<T> g = large_geom<T>(l2r.H, l2r.W, 2 * l2r.planes);
   const int64_t grid = (int64_t)g.hb_n * l2r.planes;
   if (2 * grid > 0x7fffffffLL) return hipErrorInvalidConfiguration;
   LargeHAdjParams p0 = large_hadj_params<T>(l2r, g), p1 = large_hadj_params<T>(r2l, g);

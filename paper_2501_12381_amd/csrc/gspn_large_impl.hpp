@@ -37,7 +37,8 @@ struct LargeCfg {
   static constexpr int VE = 16 / (int)sizeof(T);   // elements per 16-byte vector
   static constexpr int KH = 128 / (int)sizeof(T);  // horizontal block: columns per launch
   static constexpr int HV = KH / VE;               // 16-byte vectors per row segment
-  static constexpr int HROWS = 512;                // rows (lanes) per horizontal workgroup
+  static constexpr int HROWS = 512;                // rows (lanes) of a wide horizontal band: 8 waves
+  static constexpr int HROWS_N = 256;              // ... of a narrow one: 4 waves
   static constexpr int MAX_W = 8192 / (int)sizeof(T);  // widest row (8 KB)
 };
 
@@ -331,16 +332,32 @@ struct LargeGeom {
 };
 
 template <typename T>
-inline LargeGeom<T> large_geom(int H, int W) {
+inline int large_bands(int H, int hrows) {  // every band takes hrows lanes at most
+  constexpr int K = LargeCfg<T>::KH;
+  return H <= hrows ? 1 : (H - 2 * K + hrows - 2 * K - 1) / (hrows - 2 * K);
+}
+// `groups`: planes times directions of one launch.  A compute unit holds one
+// workgroup of a wide band or two of narrow ones.  A column's step is shorter
+// with one wave per SIMD, and two workgroups of a compute unit overlap one's
+// loads with the other's scan, but narrow bands scan more halo rows: they are
+// taken where they need no more rounds of the 256 compute units.  Forward /
+// backward with kept states, bf16, wide -> narrow: 24 planes 512 x 1024 805 ->
+// 620 / 1286 -> 1020 us, 64 planes 1024 x 1024 with logits 2061 -> 1909 / 3442
+// -> 3184 us; where a round more is needed: 100 planes 512 x 512 forward 499 ->
+// 576 us, 60 planes 720 x 1024 1020 -> 1229 us.
+template <typename T>
+inline LargeGeom<T> large_geom(int H, int W, int64_t groups) {
   using C = LargeCfg<T>;
   LargeGeom<T> g{};
-  if (H <= C::HROWS) {
-    g.hb_n = 1;
+  const int64_t wide = (large_bands<T>(H, C::HROWS) * groups + 255) / 256;
+  const int64_t narrow = (large_bands<T>(H, C::HROWS_N) * groups + 511) / 512;
+  const int hrows = narrow <= wide ? C::HROWS_N : C::HROWS;
+  g.hb_n = large_bands<T>(H, hrows);
+  if (g.hb_n == 1) {
     g.hb_mid = g.hb_edge = H;
     g.halo = 0;
   } else {
-    // every band takes HROWS lanes, the kept rows balanced over the bands
-    g.hb_n = (H - 2 * C::KH + C::HROWS - 2 * C::KH - 1) / (C::HROWS - 2 * C::KH);
+    // the kept rows balanced over the bands
     g.hb_mid = (H - 2 * C::KH + g.hb_n - 1) / g.hb_n;
     g.hb_edge = g.hb_mid + C::KH;
     g.halo = C::KH;
@@ -382,11 +399,11 @@ template <typename T>
 hipError_t large_fwd_t(const LargeFwdArgs& a) {
   using C = LargeCfg<T>;
   if (!large_fwd_supported<T>(a.H, a.W)) return hipErrorInvalidValue;
-  const LargeGeom<T> g = large_geom<T>(a.H, a.W);
   hipStream_t st = (hipStream_t)a.stream;
   const int64_t npc = a.planes * (int64_t)a.H * a.W;
   int slot[4], n = 0;
   for (int d = 0; d < 4; ++d) slot[d] = (a.mask >> d) & 1 ? n++ : -1;
+  const LargeGeom<T> g = large_geom<T>(a.H, a.W, a.planes * (slot[2] >= 0 && slot[3] >= 0 ? 2 : 1));
   const bool has_v = slot[0] >= 0 || slot[1] >= 0, has_h = slot[2] >= 0 || slot[3] >= 0;
 
   if (has_v) {

@@ -356,12 +356,13 @@ __device__ __forceinline__ void scan_h(const Maps<T>& mp, const Phase& g, float*
 
 // ---------------------------------------------------------------------------
 // forward kernel
-//   blockIdx.x -> a group of PPW = 64/SEG planes; in phase V wave 0 scans
-//   top-to-bottom and wave 1 bottom-to-top, in phase H wave 0 scans
-//   left-to-right and wave 1 right-to-left.  `slot[d]` is the index of
-//   direction d's weights in w (-1 if d is not in the mask).
-//   LDS per plane: (H + 1) x P floats, the last row and the columns >= W
-//   being padding that absorbs the writes of lanes past the end of a line.
+//   for planes of which one fp32 sum fits LDS but not two (a side is then over
+//   128: each lane holds 4 positions of a line).  One workgroup a plane; in
+//   phase V wave 0 scans top-to-bottom and wave 1 bottom-to-top, in phase H
+//   wave 0 scans left-to-right and wave 1 right-to-left.  `slot[d]` is the
+//   index of direction d's weights in w (-1 if d is not in the mask).
+//   LDS: (H + 1) x P floats, the last row and the columns >= W being padding
+//   that absorbs the writes of lanes past the end of a line.
 // ---------------------------------------------------------------------------
 // y = u * acc over one plane with VE-element vectors (W % VE == 0), in
 // batches of U vectors per thread whose loads are issued together.
@@ -393,28 +394,6 @@ __device__ __forceinline__ void epilogue(const T* __restrict__ ub, T* __restrict
   }
 }
 
-// Unmerged outputs: y_d = u_d * acc_d for the n directions of one plane in one
-// pass (u read once when it is shared), acc_d at ac + d * accsz.
-template <typename T, int VE>
-__device__ __forceinline__ void epilogue_pd(const T* __restrict__ ub, int64_t ustride, T* __restrict__ yb,
-                                            int64_t ystride, const float* __restrict__ ac, int accsz, int n,
-                                            int H, int W, int P, int tid) {
-  const int per_row = W / VE;
-  const int cnt = H * per_row;
-  for (int e = tid; e < cnt; e += 128) {
-    const int r = e / per_row, c = (e - r * per_row) * VE;
-    Pack<T, VE> uv;
-    uv.load(ub + (int64_t)r * W + c);
-    for (int d = 0; d < n; ++d) {
-      if (d > 0 && ustride) uv.load(ub + d * ustride + (int64_t)r * W + c);
-      float yv[VE];
-#pragma unroll
-      for (int q = 0; q < VE; ++q) yv[q] = uv.get(q) * ac[d * accsz + r * P + c + q];
-      stv<VE>(yb + d * ystride + (int64_t)r * W + c, yv);
-    }
-  }
-}
-
 struct ResFwdParams {
   const void* x;
   const void* lam;
@@ -432,29 +411,21 @@ struct ResFwdParams {
   // (< 128) starts a group in that direction's scan order
   uint64_t gstart[4][2];
   int logits, renorm;  // w holds Eq. 6 logits (renorm: normalised over on-line neighbours)
-  // per-direction maps (generic kernel only): lam_pd: lam is (n, B, C, H, W);
-  // y_pd: y is (n, B, C, H, W), y_d = u_d h_d, one LDS array per direction;
-  // u_pd (with y_pd): u is (n, B, C, H, W)
-  int lam_pd, u_pd, y_pd;
-  int nd;              // directions present
+  int lam_pd;          // lam is (n, B, C, H, W) (generic kernel only)
 };
 
-template <typename T, int NP, int SEG, int DV, int PDH, bool VV, int VL, int MINW, bool LG>
-__global__ void __launch_bounds__(128, MINW) resident_fwd_kernel(ResFwdParams p) {
-  constexpr int PPW = 64 / SEG;
+template <typename T, int DV, int PDH, bool VV, int VL, bool LG>
+__global__ void __launch_bounds__(128) resident_fwd_kernel(ResFwdParams p) {
+  constexpr int NP = 4;
   extern __shared__ float lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t g0 = (int64_t)blockIdx.x * PPW;
-  const int seg = lane / SEG, sl = lane % SEG;
-  const int64_t plane = (g0 + seg < p.planes) ? g0 + seg : p.planes - 1;  // clamp: stores are skipped
+  const int64_t plane = blockIdx.x;
   const int64_t HW = (int64_t)p.H * p.W;
-  const int accsz = (p.H + 1) * p.P;
-  const int narr = p.y_pd ? p.nd : 1;  // accumulator arrays per plane
 
-  for (int e = tid; e < PPW * narr * accsz; e += 128) lds[e] = 0.f;
+  for (int e = tid; e < (p.H + 1) * p.P; e += 128) lds[e] = 0.f;
   __syncthreads();
 
-  const int pos0 = sl * NP;
+  const int pos0 = lane * NP;
   const T* xb = (const T*)p.x + plane * HW;
 
 #pragma unroll
@@ -475,8 +446,7 @@ __global__ void __launch_bounds__(128, MINW) resident_fwd_kernel(ResFwdParams p)
     } else {
       const T* w0 = (const T*)p.w + (int64_t)slot * 3 * p.npc + plane * HW;
       const T* lb = (const T*)p.lam + (p.lam_pd ? slot * p.npc : 0) + plane * HW;
-      // the direction's own array (unmerged outputs) or the shared accumulator
-      float* acc = lds + (seg * narr + (p.y_pd ? slot : 0)) * accsz;
+      float* acc = lds;
       Maps<T> mp;
       mp.m[0] = xb; mp.m[1] = lb; mp.m[2] = w0; mp.m[3] = w0 + p.npc; mp.m[4] = w0 + 2 * p.npc;
       if (!hz) {
@@ -492,26 +462,13 @@ __global__ void __launch_bounds__(128, MINW) resident_fwd_kernel(ResFwdParams p)
     __syncthreads();
   }
 
-  // y = u * acc for the PPW planes of the group.  The u loads of a batch are
-  // all issued before the first is used, so the epilogue pays one memory
-  // latency per batch instead of one per element group.
-  for (int pl = 0; pl < PPW; ++pl) {
-    const int64_t pi = g0 + pl;
-    if (pi >= p.planes) break;
-    const T* ub = (const T*)p.u + pi * HW;
-    T* yb = (T*)p.y + pi * HW;
-    const float* ac = lds + pl * narr * accsz;
-    if (p.y_pd) {
-      const int64_t us = p.u_pd ? p.npc : 0;
-      if (p.vec_y == 2) epilogue_pd<T, 16 / sizeof(T)>(ub, us, yb, p.npc, ac, accsz, narr, p.H, p.W, p.P, tid);
-      else if (p.vec_y == 1) epilogue_pd<T, 8 / sizeof(T)>(ub, us, yb, p.npc, ac, accsz, narr, p.H, p.W, p.P, tid);
-      else epilogue_pd<T, 1>(ub, us, yb, p.npc, ac, accsz, narr, p.H, p.W, p.P, tid);
-      continue;
-    }
-    if (p.vec_y == 2) epilogue<T, 16 / sizeof(T)>(ub, yb, ac, p.H, p.W, p.P, tid);
-    else if (p.vec_y == 1) epilogue<T, 8 / sizeof(T)>(ub, yb, ac, p.H, p.W, p.P, tid);
-    else epilogue<T, 1>(ub, yb, ac, p.H, p.W, p.P, tid);
-  }
+  // y = u * acc.  The u loads of a batch are all issued before the first is
+  // used, so the epilogue pays one memory latency per batch.
+  const T* ub = (const T*)p.u + plane * HW;
+  T* yb = (T*)p.y + plane * HW;
+  if (p.vec_y == 2) epilogue<T, 16 / sizeof(T)>(ub, yb, lds, p.H, p.W, p.P, tid);
+  else if (p.vec_y == 1) epilogue<T, 8 / sizeof(T)>(ub, yb, lds, p.H, p.W, p.P, tid);
+  else epilogue<T, 1>(ub, yb, lds, p.H, p.W, p.P, tid);
 }
 
 }  // namespace gspn
@@ -532,7 +489,7 @@ constexpr int kMaxLds = 160 * 1024;  // LDS per CU on gfx950
 constexpr int kMaxLine = 256;        // longest line one wave holds (64 lanes x 4 positions)
 
 struct Config {
-  int np, seg, vl, lds, P;
+  int vl, lds, P;
   bool vv;
 };
 
@@ -542,10 +499,8 @@ inline bool al(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 inline bool config_for(int H, int W, size_t es, const void* const* ptrs, int nptr, Config* c, int narr = 1) {
   const int mx = H > W ? H : W;
   if (mx > kMaxLine) return false;
-  c->np = mx <= 64 ? 1 : (mx <= 128 ? 2 : 4);
-  c->seg = mx <= 15 ? 16 : (mx <= 31 ? 32 : 64);
   c->P = W + 1 + (W & 1);
-  const long lds = (long)(64 / c->seg) * narr * (H + 1) * c->P * 4;
+  const long lds = (long)narr * (H + 1) * c->P * 4;
   if (lds > kMaxLds) return false;
   c->lds = (int)lds;
   auto ptrs_al = [&](int n_el) {
@@ -557,37 +512,33 @@ inline bool config_for(int H, int W, size_t es, const void* const* ptrs, int npt
   c->vl = 1;
   for (int v : {8, 4, 2})
     if (W % v == 0 && ptrs_al(v)) { c->vl = v; break; }
-  c->vv = c->np > 1 && W % c->np == 0 && ptrs_al(c->np);
+  c->vv = W % 4 == 0 && ptrs_al(4);
   return true;
 }
 
-template <typename T, int NP, int SEG, bool VV, int VL>
+template <typename T, bool VV, int VL>
 hipError_t launch_fwd(const ResFwdParams& p, const Config& c, hipStream_t st) {
-  // DV: lines in flight in the vertical ring (5 loads each, kept under the
-  // 63 outstanding loads a wave can track); PDH: columns per horizontal row
-  // segment (32 bytes).  Packed small planes run more waves per SIMD.
-  constexpr int DV = SEG < 64 ? 6 : (NP > 2 ? 4 : 12);
-  constexpr int PDH = (VL == 1 || NP > 2) ? 16 / (int)sizeof(T) / (VL == 1 ? 2 : 1) : 32 / (int)sizeof(T);
-  constexpr int MINW = SEG < 64 ? 4 : (NP == 1 ? 2 : 1);
+  // lines in flight in the vertical ring (5 loads each, kept under the 63
+  // outstanding loads a wave can track); columns per horizontal row segment
+  constexpr int DV = 4;
+  constexpr int PDH = 16 / (int)sizeof(T) / (VL == 1 ? 2 : 1);
   constexpr int VLc = VL > 16 / (int)sizeof(T) ? 16 / (int)sizeof(T) : VL;
-  auto kern = p.logits ? resident_fwd_kernel<T, NP, SEG, DV, PDH, VV, VLc, MINW, true>
-                       : resident_fwd_kernel<T, NP, SEG, DV, PDH, VV, VLc, MINW, false>;
+  auto kern = p.logits ? resident_fwd_kernel<T, DV, PDH, VV, VLc, true> : resident_fwd_kernel<T, DV, PDH, VV, VLc, false>;
   if (c.lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, c.lds);
     if (e != hipSuccess) return e;
   }
-  const int64_t groups = (p.planes + (64 / SEG) - 1) / (64 / SEG);
-  hipLaunchKernelGGL(kern, dim3((unsigned)groups), dim3(128), c.lds, st, p);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.planes), dim3(128), c.lds, st, p);
   return hipGetLastError();
 }
 
-template <typename T, int NP, int SEG, bool VV>
+template <typename T, bool VV>
 hipError_t launch_fwd_vl(const ResFwdParams& p, const Config& c, hipStream_t st) {
   switch (c.vl) {
-    case 8: return launch_fwd<T, NP, SEG, VV, 8>(p, c, st);
-    case 4: return launch_fwd<T, NP, SEG, VV, 4>(p, c, st);
-    case 2: return launch_fwd<T, NP, SEG, VV, 2>(p, c, st);
-    default: return launch_fwd<T, NP, SEG, VV, 1>(p, c, st);
+    case 8: return launch_fwd<T, VV, 8>(p, c, st);
+    case 4: return launch_fwd<T, VV, 4>(p, c, st);
+    case 2: return launch_fwd<T, VV, 2>(p, c, st);
+    default: return launch_fwd<T, VV, 1>(p, c, st);
   }
 }
 
@@ -597,22 +548,21 @@ template <typename T>
 hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
   using namespace resident_detail;
   const void* ptrs[] = {a.x, a.lam, a.w};
-  int n = 0;
-  for (int d = 0; d < 4; ++d) n += (a.mask >> d) & 1;
-  const bool pd = a.lam_pd || a.u_pd || a.y_pd;
+  const bool pd = a.lam_pd != 0;
   if (a.u_pd && !a.y_pd) return hipErrorInvalidValue;  // a merged y with per-direction u: streaming family
   Config c;
-  if (a.y_pd && quad_fwd_fits(a.H, a.W, true)) return sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
-  if (!config_for(a.H, a.W, sizeof(T), ptrs, 3, &c, a.y_pd ? n : 1)) return hipErrorInvalidValue;
+  // unmerged outputs need no sum: the generic kernels take every line one wave holds
+  if (a.y_pd) return !quad_fwd_fits(a.H, a.W, true) ? hipErrorInvalidValue
+                   : sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
+  if (!config_for(a.H, a.W, sizeof(T), ptrs, 3, &c)) return hipErrorInvalidValue;
   ResFwdParams p;
   p.x = a.x; p.lam = a.lam; p.w = a.w; p.u = a.u; p.y = a.y;
   p.npc = (int64_t)a.planes * a.H * a.W;
   p.planes = a.planes;
   p.H = a.H; p.W = a.W; p.P = c.P;
-  n = 0;
+  int n = 0;
   for (int d = 0; d < 4; ++d) p.slot[d] = (a.mask >> d) & 1 ? n++ : -1;
-  p.nd = n;
-  p.lam_pd = a.lam_pd; p.u_pd = a.u_pd; p.y_pd = a.y_pd;
+  p.lam_pd = a.lam_pd;
   p.gh = (a.group_h > 0 && a.group_h < a.H) ? a.group_h : a.H;
   p.gw = (a.group_w > 0 && a.group_w < a.W) ? a.group_w : a.W;
   p.grouped = p.gh < a.H || p.gw < a.W;
@@ -627,12 +577,9 @@ hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
   }
   // epilogue vectors: 16 bytes if rows allow, else 8 bytes, else scalars
   const int v16 = 16 / (int)sizeof(T), v8 = 8 / (int)sizeof(T);
-  // per-direction maps start npc elements apart: their starts must keep the alignment too
-  const size_t mapb = (size_t)p.npc * sizeof(T);
-  p.vec_y = (a.W % v16 == 0 && al(a.u, 16) && al(a.y, 16) && (!pd || mapb % 16 == 0)) ? 2
-          : (a.W % v8 == 0 && al(a.u, 8) && al(a.y, 8) && (!pd || mapb % 8 == 0)) ? 1 : 0;
+  p.vec_y = (a.W % v16 == 0 && al(a.u, 16) && al(a.y, 16)) ? 2 : (a.W % v8 == 0 && al(a.u, 8) && al(a.y, 8)) ? 1 : 0;
   hipStream_t st = (hipStream_t)a.stream;
-  // per-direction maps run on the generic kernels only
+  // a lam per direction runs on the generic kernels only
   if (!pd && a.use_fixed && !p.grouped && a.H == 128 && a.W == 128 && al(a.x, 16) && al(a.lam, 16) &&
       al(a.w, 16) && al(a.u, 16) && al(a.y, 16))
     return launch_wide<T>(p, st);  // persistent, every input read once
@@ -645,9 +592,9 @@ hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
       default: return launch_fixed<T, 64>(p, st);
     }
   }
-  if (quad_fwd_fits(a.H, a.W, a.y_pd)) return sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
-  // one sum fits LDS, two do not: planes with a side over 128
-  return c.vv ? launch_fwd_vl<T, 4, 64, true>(p, c, st) : launch_fwd_vl<T, 4, 64, false>(p, c, st);
+  if (quad_fwd_fits(a.H, a.W, false)) return sizeof(T) == 4 ? quad_fwd_f32(a) : quad_fwd_bf16(a);
+  if (a.H <= 128 && a.W <= 128) return hipErrorInvalidValue;  // (two sums of such planes always fit)
+  return c.vv ? launch_fwd_vl<T, true>(p, c, st) : launch_fwd_vl<T, false>(p, c, st);
 }
 
 // narr: accumulator arrays per plane (the directions present, for unmerged outputs)

@@ -452,8 +452,54 @@ hipError_t launch_vscan_r(const VScanParams& p, int out, bool lg, int waves, hip
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * waves), 0, st, p);
   return hipGetLastError();
 }
+// Column bands (gspn_vband_impl.hpp) for few planes.
+struct VBandCfg {
+  static constexpr int G = 2;   // columns per lane
+  static constexpr int NW = 4;  // waves per workgroup, one per SIMD
+  static constexpr int SPAN = NW * (64 - 2 * VSpan<G>::HL);  // lanes of a workgroup's span
+};
+
+struct VBandGeom {
+  int rows;  // rows per launch
+  int hb;    // halo lanes of a band: one column a row
+  int nb;    // bands
+  int mid;   // lanes kept by an inner band; the first and last keep hb more (they have one halo)
+};
+inline VBandGeom vband_geom(int W, int rows) {
+  using C = VBandCfg;
+  const int lt = W / C::G, hb = rows / C::G;
+  if (lt <= C::SPAN) return {rows, hb, 1, lt};
+  const int nb = (lt - 2 * hb + C::SPAN - 2 * hb - 1) / (C::SPAN - 2 * hb);
+  return {rows, hb, nb, (lt - 2 * hb + nb - 1) / nb};
+}
+
+// The bands of a launch, none (nb == 0) where the one-workgroup pass is the
+// better one.  Bands are taken where a plane's row needs more than one wave per
+// SIMD and every band still gets a compute unit of its own: 128 rows a launch,
+// or 64 when their wider bands are what fits.  The whole forward, one workgroup
+// a plane and direction -> bands of 64 -> of 128 rows, bf16: 1 plane 2048 x 2048
+// with logits 2622 -> 1450 -> 1416 us, 16 planes 1024 x 1024 829 -> 722 -> 687,
+// 20 planes 1024 x 2048 (128 rows: 400 bands) 1769 -> 1375 us.  Left as they
+// were: 64 planes 1024 x 1024 1900 -> 1879 us (384 bands), 24 planes 512 x 512
+// fp32 410 -> 447 us (3 waves a row).
+inline VBandGeom vband_choose(const VScanParams& p) {
+  const int64_t groups = p.planes * (p.slot[0] >= 0 && p.slot[1] >= 0 ? 2 : 1);
+  if (vpass_geom(p.W).waves > 4)
+    for (int rows : {128, 64}) {
+      const VBandGeom g = vband_geom(p.W, rows);
+      if (groups * g.nb <= 256) return g;
+    }
+  return {0, 0, 0, 0};
+}
+template <typename T>
+hipError_t launch_vband(const VScanParams& p, const VBandGeom& g, bool lg, hipStream_t st);
+
 template <typename T>
 hipError_t launch_vscan(VScanParams p, int out, bool lg, hipStream_t st) {
+  if (out == 0) {
+    const VBandGeom b = vband_choose(p);
+    if (b.nb > 0) return launch_vband<T>(p, b, lg, st);
+  }
   const VGeom v = vpass_geom(p.W);
   p.k = v.k;
   if constexpr (sizeof(T) == 4) {  // rows of at most 2048 columns: 9 waves
