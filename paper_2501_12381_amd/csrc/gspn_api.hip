@@ -157,13 +157,13 @@ int check_ws(void* ws, size_t ws_bytes, size_t need,
 constexpr uint32_t kEq6Flags = GSPN_FLAG_W_LOGITS | GSPN_FLAG_EDGE_RENORM;
 constexpr uint32_t kPdFlags = GSPN_FLAG_LAM_PER_DIR | GSPN_FLAG_U_PER_DIR | GSPN_FLAG_Y_PER_DIR;
 
-bool resident_fits(const Problem& p, int dtype, bool backward) {
+bool resident_fits(const Problem& p, bool backward) {
   if (p.flags & kPdFlags) {
     if (!backward && p.u_pd() && !p.y_pd()) return false;
     if (backward && p.H == 128 && p.W == 128) return false;  // the persistent backward merges
   }
   if (p.grouped() && !(backward ? kResidentGroupsBwd : kResidentGroupsFwd)) return false;
-  return gspn::resident_fits((int)p.H, (int)p.W, dtype, backward, (!backward && p.y_pd()) ? p.n : 1);
+  return gspn::resident_fits((int)p.H, (int)p.W, backward, (!backward && p.y_pd()) ? p.n : 1);
 }
 
 // the two-pass family takes unmerged outputs (per-direction y and dy) but not
@@ -185,9 +185,9 @@ constexpr int kAlgoQuad = 100, kAlgoPair = 101;
 int choose_algo(const Problem& p, int dtype, int algo, bool backward) {
   if (algo == GSPN_ALGO_STREAM) return GSPN_ALGO_STREAM;
   if (algo == GSPN_ALGO_RESIDENT || algo == GSPN_ALGO_RESIDENT_GENERIC)
-    return resident_fits(p, dtype, backward) ? algo : -1;
+    return resident_fits(p, backward) ? algo : -1;
   if (algo == GSPN_ALGO_TWO_PASS) return two_pass_fits(p, dtype, backward) ? algo : -1;
-  if (resident_fits(p, dtype, backward)) return GSPN_ALGO_RESIDENT;
+  if (resident_fits(p, backward)) return GSPN_ALGO_RESIDENT;
   const int H = (int)p.H, W = (int)p.W;
   if (backward) {
     if (gspn::quad_bwd_fits(H, W)) return kAlgoQuad;

@@ -157,7 +157,7 @@ bool pair_bwd_fits(int H, int W);
 
 // narr: accumulator arrays per plane of the forward (the directions present
 // for unmerged outputs, else 1)
-bool resident_fits(int H, int W, int dtype, bool backward, int narr);
+bool resident_fits(int H, int W, bool backward, int narr);
 
 // ---- two-pass family: planes too large for LDS -------------------------------
 struct LargeFwdArgs {

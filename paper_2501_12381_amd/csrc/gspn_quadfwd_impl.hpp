@@ -7,10 +7,16 @@
 // only in the middle; y = u * (vertical sum + horizontal sum).  Unmerged outputs (y_d = u_d h_d) need no array at all: each wave
 // multiplies its h by u and stores it.
 //
-// Duo kernel (larger planes whose lam * x and sum fit LDS): lam * x is formed
-// once into LDS (x and lam are read once, not once per direction), then the
-// vertical pair scans, then the horizontal one, each direction on two waves
-// (half of a line each, see QHalf), adding into one array (QMerge).
+// Duo kernel (larger planes of which one sum fits LDS): the vertical pair scans,
+// then the horizontal one, each direction on two waves (half of a line each,
+// see QHalf), adding into one array (QMerge).  What bounds it is how few waves a
+// compute unit holds, so LDS is spent on a second workgroup rather than on
+// sharing lam * x: x and lam are read once per axis.  Only where two arrays a
+// plane leave room for two workgroups (the registers' limit) is lam * x formed
+// once into the second one (LX).  One array against two: 1280 planes of 96 x
+// 168 bf16 344 -> 251 us, 640 of 104 x 152 202 -> 152, 640 of 112 x 112 145 ->
+// 110; planes of which two arrays do not fit ran on two waves before: 300 planes of
+// 160 x 160 328 -> 194 us, 200 x 192 with logits 589 -> 330 us.
 #pragma once
 
 #include "gspn_quad_impl.hpp"
@@ -29,6 +35,7 @@ struct QFwdParams {
   int gh, gw;        // group lengths (the line count: global)
   int renorm;
   int lam_pd, u_pd;  // per-direction maps (u_pd: unmerged outputs only)
+  int split;         // duo: lines of at least 32 positions go to two waves
 };
 
 // TV: vectors of a row in the registers of a horizontal wave (narrow planes
@@ -146,25 +153,26 @@ __global__ void __launch_bounds__(256, NPH > 1 ? 1 : (TV <= 4 ? 4 : 2)) quad_fwd
 
 // Waves of an axis: split lines (at least 32 positions) go to two waves per
 // direction, shorter ones to one (the second keeps the barriers in step).
-template <typename T, int NPV, int NPH, int VL, bool LG>
+template <typename T, int NPV, int NPH, int VL, bool LG, bool LX>
 __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
   constexpr int ES = (int)sizeof(T), VE = VL;
-  extern __shared__ float lds[];
-  __shared__ float xbuf[2][2 * 2 * kHalo];
+  extern __shared__ float lds[];  // the sum, lam * x (LX), the exchange buffers of split lines
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int HW = p.H * p.W;
   const int64_t gof = (int64_t)blockIdx.x * HW;
   const QPlanes g{p.H, p.W, p.P, 1, 6};
   const int bytes = HW * ES;
   const int ARR = (p.H + 1) * p.P;
-  float *const lxa = lds, *const acc = lds + ARR;
+  float *const acc = lds, *const lxa = lds + ARR;
   const int dir = wave >> 1, hf = wave & 1;
+  float* const xbuf = lds + (LX ? 2 : 1) * ARR + dir * (2 * 2 * kHalo);
   const bool rev = dir != 0, rn = p.renorm != 0;
   auto barrier = []() __attribute__((always_inline)) { lds_barrier(); };
 
-  for (int i = threadIdx.x; i < p.P; i += 256) lxa[p.H * p.P + i] = 0.f;  // idle rows read the padding row
-  {  // lam * x
-    const wide_rsrc_t rx = q_rsrc((const T*)p.x + gof, bytes), rl = q_rsrc((const T*)p.lam + gof, bytes);
+  const wide_rsrc_t rx = q_rsrc((const T*)p.x + gof, bytes);
+  if constexpr (LX) {
+    for (int i = threadIdx.x; i < p.P; i += 256) lxa[p.H * p.P + i] = 0.f;  // idle rows read the padding row
+    const wide_rsrc_t rl = q_rsrc((const T*)p.lam + gof, bytes);
     constexpr int U = 4;
     QPack<T, VE> vx[U], vl[U];
     q_flat<VE, U>(
@@ -177,8 +185,8 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
 #pragma unroll
           for (int q = 0; q < VE; ++q) lxa[li[q]] = vl[k].get(q) * vx[k].get(q);
         });
+    __syncthreads();
   }
-  __syncthreads();
 
   const bool hv = p.slot[0] >= 0 || p.slot[1] >= 0;
   // one axis: the pair's scans with exchanges and middle-line barriers
@@ -186,7 +194,7 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
     constexpr bool HZ = decltype(hzt)::value;
     constexpr int NP = HZ ? NPH : NPV;
     const int L = HZ ? p.W : p.H, Pn = HZ ? p.H : p.W, grp = HZ ? p.gw : p.gh;
-    const bool split = Pn >= 32;
+    const bool split = Pn >= 32 && p.split;
     const int slot = p.slot[(HZ ? 2 : 0) + dir];
     const int nt = (p.W + VL - 1) / VL;  // vectors of a horizontal scan
     if (slot < 0 || (!split && hf)) {
@@ -198,8 +206,13 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
     }
     const T* w0 = (const T*)p.w + (int64_t)slot * 3 * p.npc + gof;
     const wide_rsrc_t rw0 = q_rsrc(w0, bytes);
-    const wide_rsrc_t rb[6] = {rw0, rw0, rw0, q_rsrc(w0 + p.npc, bytes), q_rsrc(w0 + 2 * p.npc, bytes), rw0};
-    const QHalf half{hf, ((Pn + 1) / 2 + NP - 1) / NP * NP, xbuf[dir]};
+    const wide_rsrc_t rb[6] = {LX ? rw0 : rx,
+                               LX ? rw0 : q_rsrc((const T*)p.lam + (p.lam_pd ? slot * p.npc : 0) + gof, bytes),
+                               rw0,
+                               q_rsrc(w0 + p.npc, bytes),
+                               q_rsrc(w0 + 2 * p.npc, bytes),
+                               rw0};
+    const QHalf half{hf, ((Pn + 1) / 2 + NP - 1) / NP * NP, xbuf};
     auto exchange = [&](int par, auto& v, int pos0) __attribute__((always_inline)) {
       if (split) q_exchange<NP>(v, half, pos0, par, barrier);
     };
@@ -214,7 +227,9 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
         lx.off[q] = (ln.valid[q] ? ln.pos0 + q : 0) * g.P;
         m.off[q] = (ln.voffs[q] != kWideOob ? ln.pos0 + q : g.H) * g.P;
       }
-      qh_forward<T, NP, VL, NP == 4 ? 3 : 8, NP == 1 ? 2 : 1, LG, false, true>(
+      // vectors in a group of loads: 5 maps (LX: 3) in under 200 registers
+      constexpr int TV = LX ? (NP == 4 ? 3 : 8) : (NP == 1 ? 8 : (NP == 2 ? 4 : 1));
+      qh_forward<T, NP, VL, TV, LX && NP == 1 ? 2 : 1, LG, false, LX>(
           rb, ln, g, rev, grp, rn, lx,
           [&](int ti, int n, int col) __attribute__((always_inline)) { m.begin(ti, n, col); },
           [&](int col, int, bool, const float (&h)[NP], const QPack<T, VL> (&)[NP]) __attribute__((always_inline)) {
@@ -229,7 +244,7 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
         lx.off[q] = ln.valid[q] ? ln.pos0 + q : 0;
         m.off[q] = ln.valid[q] && ln.kept ? ln.pos0 + q : g.W;
       }
-      qv_forward<T, NP, QRing<T, NP>::RV, LG, false, true>(
+      qv_forward<T, NP, QRing<T, NP>::RV, LG, false, LX>(
           rb, ln, g, rev, grp, rn, lx,
           [&](int b, int n, int line) __attribute__((always_inline)) { m.begin(b, n, line * g.P); },
           [&](int line, int next, int, const float (&h)[NP], const QPack<T, NP>&) __attribute__((always_inline)) {
@@ -284,10 +299,11 @@ inline int64_t quad_lds(const QConfig& c, int H, int arrays) {
   return (int64_t)(64 >> c.segsh) * arrays * (H + 1) * c.P * 4;
 }
 constexpr int kQuadMaxLds = 160 * 1024;
+constexpr int kDuoXbuf = 2 * 2 * 2 * kHalo * 4;  // exchange buffers of the duo kernel
 
 inline bool quad_fwd_size_fits(int H, int W, bool unmerged) {
   QConfig c;
-  return quad_config(H, W, &c) && (unmerged || quad_lds(c, H, 2) <= kQuadMaxLds);
+  return quad_config(H, W, &c) && (unmerged || quad_lds(c, H, 1) <= kQuadMaxLds);
 }
 
 template <typename T, int NPV, int NPH, int VL, bool LG, bool PD, int TV = QVecs<NPH>::TV>
@@ -301,9 +317,9 @@ hipError_t launch_quad_fwd_k(const QFwdParams& p, int lds, hipStream_t st) {
   hipLaunchKernelGGL(kern, dim3((unsigned)((p.planes + ppw - 1) / ppw)), dim3(256), lds, st, p);
   return hipGetLastError();
 }
-template <typename T, int NPV, int NPH, bool LG>
+template <typename T, int NPV, int NPH, bool LG, bool LX>
 hipError_t launch_duo_fwd_k(const QFwdParams& p, int lds, hipStream_t st) {
-  auto kern = duo_fwd_kernel<T, NPV, NPH, 16 / (int)sizeof(T), LG>;
+  auto kern = duo_fwd_kernel<T, NPV, NPH, 16 / (int)sizeof(T), LG, LX>;
   if (lds > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
     if (e != hipSuccess) return e;
@@ -312,8 +328,25 @@ hipError_t launch_duo_fwd_k(const QFwdParams& p, int lds, hipStream_t st) {
   return hipGetLastError();
 }
 
-// merged outputs: lines of at most 64 positions on the quad kernel (and lam
-// per direction, and rows narrower than a vector), longer ones on the duo kernel
+// positions a lane of a wave that holds half a line and the halo of the other half
+inline int duo_np(int n) { return n < 32 || (n + 1) / 2 + kHalo <= 64 ? 1 : ((n + 1) / 2 + 1 + kHalo <= 128 ? 2 : 4); }
+
+template <typename T, bool LG, bool LX>
+hipError_t launch_duo_fwd(const QFwdParams& p, int lds, hipStream_t st) {
+  const int v = p.split ? duo_np(p.W) : 4, h = p.split ? duo_np(p.H) : 4;
+  if (v == 1)
+    return h == 1 ? launch_duo_fwd_k<T, 1, 1, LG, LX>(p, lds, st)
+         : h == 2 ? launch_duo_fwd_k<T, 1, 2, LG, LX>(p, lds, st) : launch_duo_fwd_k<T, 1, 4, LG, LX>(p, lds, st);
+  if (v == 2 && h == 1) return launch_duo_fwd_k<T, 2, 1, LG, LX>(p, lds, st);
+  if (v == 4 && h == 1) return launch_duo_fwd_k<T, 4, 1, LG, LX>(p, lds, st);
+  if (v == 2 && h == 2) return launch_duo_fwd_k<T, 2, 2, LG, LX>(p, lds, st);
+  // a side over 240 beside one over 112, or lines kept whole
+  if constexpr (LX) return hipErrorInvalidValue;  // (two arrays of such planes exceed LDS)
+  else return launch_duo_fwd_k<T, 4, 4, LG, LX>(p, lds, st);
+}
+
+// merged outputs: lines of at most 64 positions on the quad kernel (and rows
+// narrower than a vector), longer ones on the duo kernel
 template <typename T, bool LG>
 hipError_t launch_quad_fwd(QFwdParams p, hipStream_t st) {
   QConfig c;
@@ -321,41 +354,28 @@ hipError_t launch_quad_fwd(QFwdParams p, hipStream_t st) {
   if (!quad_config(p.H, p.W, &c)) return hipErrorInvalidValue;
   p.P = c.P;
   p.segsh = c.segsh;
-  const int64_t lds64 = quad_lds(c, p.H, 2);
-  if (lds64 > kQuadMaxLds) return hipErrorInvalidValue;
-  const int lds = (int)lds64;
-  if constexpr (VL > 4) {  // bf16 rows of 4 to 7: 8-byte vectors
-    if (p.W < VL && p.W >= 4 && c.nph == 1) return launch_quad_fwd_k<T, 1, 1, 4, LG, false, 2>(p, lds, st);
-  }
-  if (p.W < VL)  // the horizontal scans go column by column
-    return c.nph == 1 ? launch_quad_fwd_k<T, 1, 1, 1, LG, false>(p, lds, st)
-         : c.nph == 2 ? launch_quad_fwd_k<T, 1, 2, 1, LG, false>(p, lds, st)
-                      : launch_quad_fwd_k<T, 1, 4, 1, LG, false>(p, lds, st);
-  if (c.npv == 1 && c.nph == 1)
+  const int64_t one = quad_lds(c, p.H, 1);
+  if (one > kQuadMaxLds) return hipErrorInvalidValue;
+  if (p.W < VL || (c.npv == 1 && c.nph == 1)) {
+    const int lds = (int)(2 * one);  // (at most 34 KB)
+    if constexpr (VL > 4) {  // bf16 rows of 4 to 7: 8-byte vectors
+      if (p.W < VL && p.W >= 4 && c.nph == 1) return launch_quad_fwd_k<T, 1, 1, 4, LG, false, 2>(p, lds, st);
+    }
+    if (p.W < VL)  // the horizontal scans go column by column
+      return c.nph == 1 ? launch_quad_fwd_k<T, 1, 1, 1, LG, false>(p, lds, st)
+           : c.nph == 2 ? launch_quad_fwd_k<T, 1, 2, 1, LG, false>(p, lds, st)
+                        : launch_quad_fwd_k<T, 1, 4, 1, LG, false>(p, lds, st);
     return p.W <= 2 * VL ? launch_quad_fwd_k<T, 1, 1, VL, LG, false, 2>(p, lds, st)
          : p.W <= 4 * VL ? launch_quad_fwd_k<T, 1, 1, VL, LG, false, 4>(p, lds, st)
                          : launch_quad_fwd_k<T, 1, 1, VL, LG, false>(p, lds, st);
-  if (p.lam_pd) {  // one lam a direction: no lam * x to share
-    auto h = [&](auto npv) -> hipError_t {
-      constexpr int V = decltype(npv)::value;
-      return c.nph == 1 ? launch_quad_fwd_k<T, V, 1, VL, LG, false>(p, lds, st)
-           : c.nph == 2 ? launch_quad_fwd_k<T, V, 2, VL, LG, false>(p, lds, st)
-                        : launch_quad_fwd_k<T, V, 4, VL, LG, false>(p, lds, st);
-    };
-    return c.npv == 1 ? h(std::integral_constant<int, 1>{})
-         : c.npv == 2 ? h(std::integral_constant<int, 2>{}) : h(std::integral_constant<int, 4>{});
   }
-  // half a line and the halo of the other half in a wave
-  auto np = [](int n) { return n < 32 || (n + 1) / 2 + kHalo <= 64 ? 1 : ((n + 1) / 2 + 1 + kHalo <= 128 ? 2 : 4); };
-  const int v = np(p.W), h = np(p.H);
-  if (v == 1)
-    return h == 1 ? launch_duo_fwd_k<T, 1, 1, LG>(p, lds, st)
-         : h == 2 ? launch_duo_fwd_k<T, 1, 2, LG>(p, lds, st) : launch_duo_fwd_k<T, 1, 4, LG>(p, lds, st);
-  if (v == 2)
-    return h == 1 ? launch_duo_fwd_k<T, 2, 1, LG>(p, lds, st)
-         : h == 2 ? launch_duo_fwd_k<T, 2, 2, LG>(p, lds, st) : launch_duo_fwd_k<T, 2, 4, LG>(p, lds, st);
-  // two arrays of a plane with one side over 240 leave under 80 for the other
-  return h == 1 ? launch_duo_fwd_k<T, 4, 1, LG>(p, lds, st) : hipErrorInvalidValue;
+  p.split = one + kDuoXbuf <= kQuadMaxLds;  // else the lines stay whole: the sum fills LDS to the last bytes
+  // the second array costs no workgroup: two of them share a compute unit all
+  // the same, or the planes are at most one each (160 planes 136 x 144 fp32: one
+  // array 101 us, two 95; 600 planes bf16: 193 against 246)
+  if (!p.lam_pd && 2 * one + kDuoXbuf <= (p.planes <= 256 ? kQuadMaxLds : kQuadMaxLds / 2))
+    return launch_duo_fwd<T, LG, true>(p, (int)(2 * one) + kDuoXbuf, st);
+  return launch_duo_fwd<T, LG, false>(p, (int)one + (p.split ? kDuoXbuf : 0), st);
 }
 
 // unmerged outputs

@@ -1,6 +1,6 @@
-// Resident-family forward dispatch and the generic resident kernels, bf16 storage (fp32 arithmetic).
-// The size-specialised and persistent 128 x 128 kernels are instantiated in
-// their own translation units (gspn_fixed_*, gspn_widefwd_*).
+// Resident-family forward dispatch, bf16 storage (fp32 arithmetic).
+// The kernels are instantiated in their own translation units (gspn_fixed_*,
+// gspn_widefwd_*, gspn_quadfwd*).
 #include "gspn_resident_impl.hpp"
 
 namespace gspn {

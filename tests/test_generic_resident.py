@@ -81,3 +81,37 @@ def test_generic_resident_per_direction(shape, pd):
         for name, g, r in zip(("y", "dx", "dw", "dlam", "du"), (y,) + tuple(got), ref):
             e = normwise(g, r)
             assert e <= TOL[dtype], f"{name}: {e:.3e}"
+
+
+# one sum in LDS (x and lam read once per axis): two arrays would fit but the
+# planes are more than the compute units, only one fits, a side over 240 beside
+# one over 112, and sums that leave no room for the exchange buffers (lines
+# kept whole)
+ONE_SUM = [(258, 104, 102, 15, 0, 0, False), (2, 160, 160, 15, 0, 0, True), (1, 200, 193, 13, 90, 50, False),
+           (1, 250, 150, 15, 0, 0, False), (1, 130, 256, 7, 0, 0, True), (1, 209, 194, 15, 0, 0, False),
+           (2, 193, 209, 11, 100, 60, True)]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16], ids=["f32", "bf16"])
+@pytest.mark.parametrize("case", ONE_SUM, ids=lambda c: "x".join(map(str, c)))
+def test_generic_forward_one_sum(case, dtype):
+    planes, H, W, mask, gh, gw, logits = case
+    print(f"[one sum] {case} {dtype}", flush=True)
+    n = bin(mask).count("1")
+    inp = synth.random_general((1, planes, H, W), n, device=DEV, seed=H * 300 + W, dtype=dtype)
+    lams = torch.stack([inp["lam"] * (0.5 + 0.25 * d) for d in range(n)])
+    opt = dict(group_h=gh, group_w=gw, logits=logits)
+    for lam, pd in ((inp["lam"], False), (lams, True)):
+        if pd and planes > 2:
+            continue
+        for shift in (False, True):
+            args = [inp["x"], inp["w"], lam, inp["u"]]
+            if shift:
+                args = [misalign(t) for t in args]
+            y = ops.gspn_scan_fwd(*args, mask, lam_per_dir=pd, **opt)
+            torch.cuda.synchronize()
+            if not shift:
+                first = y
+                e = normwise(y, O.scan_fwd(*[np64(t) for t in args], mask, lam_per_dir=pd, **opt))
+                assert torch.isfinite(y).all() and e <= TOL[dtype], f"{e:.3e}"
+            assert torch.equal(y, first)
