@@ -274,7 +274,12 @@ struct QRows {
 // too).  begin(block, blocks, first line) before every block, emit(line, next
 // line, row offset, h, u pack) after every row, end(block, blocks) after every
 // block.
-template <typename T, int NP, int R, bool LG, bool UM, bool LX, typename FB, typename F, typename FE,
+// XE: the exchange precedes the last row's emit (whose receiver keeps the halo
+// positions too), else it follows end().  With a QMerge it has to follow: in the
+// middle block the exchange's barrier would otherwise come before the merge's
+// second one and pair with the opposite direction's, which then reads the
+// block's last row while it is still being stored.
+template <typename T, int NP, int R, bool LG, bool UM, bool LX, bool XE = false, typename FB, typename F, typename FE,
           typename FX = QNoExchange>
 __device__ __forceinline__ void qv_forward(const wide_rsrc_t (&rb)[6], const QV<T, NP>& ln, const QPlanes& g,
                                            bool rev, int grp, bool renorm, const QLamX<NP>& lam_x, FB&& begin,
@@ -339,10 +344,11 @@ __device__ __forceinline__ void qv_forward(const wide_rsrc_t (&rb)[6], const QV<
         norm_weights<LG, NP>(a, b, c, ln.pos0, W, renorm);
         line_step<NP>(xv, lv, a, b, c, ln.valid, hp);
         load(k, s + R);
-        if (kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange(ub & 1, hp);
+        if (XE && kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange(ub & 1, hp);
         emit(rows.line(s), rows.line(s + 1), rows.soff(s), hp, v[NM - 1]);
       }
       end(b0 + ub, rows.nb);
+      if (!XE && b0 + ub + 1 < rows.nb) exchange(ub & 1, hp);
     }
   }
 }
@@ -753,6 +759,9 @@ __device__ __forceinline__ void q_flat(const QPlanes& g, int tid, int nthreads, 
 // element gets its terms in a fixed order.  The first to come stores (or adds,
 // when the array holds a sum already), the other adds, reading one line ahead
 // but never across the barriers.
+// The barriers are anonymous: every wave of the pair, the idle ones too, has to
+// pass them and those of an edge exchange in one sequence, in which a block's
+// exchange follows its end().
 template <int NP>
 struct QMerge {
   float* arr;

@@ -263,7 +263,7 @@ __global__ void __launch_bounds__(256, 1) pair_bwd_kernel(QBwdParams p, int fini
           },
           [](int, int, bool, int) {}, exchange);
     } else {
-      qv_forward<T, NP, QRing<T, NP>::RV, LG, false, false>(
+      qv_forward<T, NP, QRing<T, NP>::RV, LG, false, false, true>(
           rb, ln, g, rev, grp, rn, QLamX<NP>{}, [](int, int, int) {},
           [&](int line, int, int, const float (&h)[NP], const QPack<T, NP>&) __attribute__((always_inline)) {
             float* d = arr + line * g.P;

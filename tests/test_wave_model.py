@@ -1,0 +1,98 @@
+"""The generic resident kernels' own source, compiled for the host and run with
+a workgroup's waves one after the other between two barriers, in several
+orders (tests/wave_model).  What two waves leave unordered gives another result
+in one of the orders; on the GPU the waves' timing can hide it.  Every order
+has to give the same bits, and those the oracle's within the rounding of the
+stored values."""
+import ctypes
+import os
+import subprocess
+from concurrent.futures import ThreadPoolExecutor
+
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+from paper_2501_12381_amd import build as B, synth
+from .parity_util import np64, normwise
+
+HERE = os.path.join(os.path.dirname(os.path.abspath(__file__)), "wave_model")
+F32, BF16 = torch.float32, torch.bfloat16
+# fp32: the chain's rounding, as in the other parity tests; bf16: half a unit in
+# the last place of the largest value on top of it
+TOL = {F32: 1e-5, BF16: 2.0 ** -8 + 1e-5}
+# waves in the order in which they run between barriers: either direction of a
+# pair first, either half of a line first
+ORDERS = [(0, 1, 2, 3), (3, 2, 1, 0), (2, 3, 0, 1), (1, 0, 3, 2)]
+
+
+def clang():
+    for c in ("/opt/rocm/llvm/bin/clang++", os.path.join(os.path.dirname(B.hipcc()), "amdclang++")):
+        if os.path.exists(c):
+            return c
+    raise RuntimeError("no clang++ beside hipcc")
+
+
+@pytest.fixture(scope="module")
+def model(tmp_path_factory):
+    """{(dtype, logits): library}"""
+    d = str(tmp_path_factory.mktemp("wave_model"))
+    for f in os.listdir(B.CSRC):
+        if f.endswith(".hpp"):
+            text = open(os.path.join(B.CSRC, f)).read()
+            text = text.replace("extern __shared__", "extern")
+            text = text.replace('asm volatile("s_waitcnt lgkmcnt(0)\\n\\ts_barrier" ::: "memory");', "sim::barrier();")
+            assert "s_barrier\"" not in text, f
+            open(os.path.join(d, f), "w").write(text)
+
+    def compile_one(key):
+        out = os.path.join(d, f"model_{len(str(key[0]))}_{int(key[1])}.so")
+        subprocess.run([clang(), "-x", "c++", "-std=c++17", "-O0", "-w", "-fPIC", "-shared",
+                        f"-DMODEL_T={int(key[0] == BF16)}", f"-DMODEL_LG={'true' if key[1] else 'false'}",
+                        "-I", HERE, "-I", d, os.path.join(HERE, "model.cpp"), "-o", out], check=True)
+        return ctypes.CDLL(out)
+
+    keys = [(t, lg) for t in (F32, BF16) for lg in (False, True)]
+    with ThreadPoolExecutor(4) as ex:
+        return dict(zip(keys, ex.map(compile_one, keys)))
+
+
+def ptr(t):
+    return ctypes.c_void_p(t.data_ptr())
+
+
+def inputs(case, dtype):
+    planes, H, W, mask, gh, gw, logits = case
+    n = bin(mask).count("1")
+    inp = synth.random_general((1, planes, H, W), n, device="cpu", seed=H * 300 + W, dtype=dtype)
+    return inp, {k: np64(v) for k, v in inp.items()}, dict(group_h=gh, group_w=gw, logits=logits)
+
+
+def run_forward(model, case, dtype, inp, order):
+    planes, H, W, mask, gh, gw, logits = case
+    y = torch.full_like(inp["x"], float("nan"))
+    st = model[dtype, logits].model_fwd(ptr(inp["x"]), ptr(inp["w"]), ptr(inp["lam"]), ptr(inp["u"]), ptr(y),
+                                        ctypes.c_int64(planes), H, W, mask, gh, gw, 0, 0, (ctypes.c_int * 4)(*order))
+    assert st == 0
+    return y
+
+
+def check_forward(model, case, dtype):
+    inp, a, opt = inputs(case, dtype)
+    ys = [run_forward(model, case, dtype, inp, o) for o in ORDERS]
+    e = normwise(ys[0], O.scan_fwd(a["x"], a["w"], a["lam"], a["u"], case[3], **opt))
+    assert torch.isfinite(ys[0]).all() and e <= TOL[dtype], f"{case}: {e:.3e}"
+    for o, y in zip(ORDERS, ys):
+        assert torch.equal(ys[0], y), f"{case}: the waves in the order {o} give another result"
+
+
+# (planes, H, W, mask, group_h, group_w, logits): one, two and three blocks of
+# eight rows, on lines that two waves share
+@pytest.mark.parametrize("case,dtype", [((1, 8, 120, 15, 0, 0, False), F32), ((1, 16, 120, 15, 0, 0, True), F32),
+                                        ((1, 24, 120, 3, 0, 0, False), F32), ((1, 19, 113, 15, 7, 40, True), F32),
+                                        ((1, 24, 250, 15, 0, 0, False), F32), ((1, 24, 240, 15, 0, 0, True), BF16),
+                                        ((1, 17, 200, 15, 0, 0, False), BF16), ((1, 24, 120, 14, 0, 0, False), F32)],
+                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v)[6:])
+def test_merge_order(model, case, dtype):
+    check_forward(model, case, dtype)
