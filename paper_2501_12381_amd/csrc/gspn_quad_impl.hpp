@@ -109,6 +109,9 @@ struct QPlanes {
 // scans its span alone; every kHalo lines they exchange their edges.  A wave
 // has LDS columns (rows, for a horizontal scan) of its own for its whole span:
 // position p of wave 1's lie 2 kHalo further on.
+// An exchange has one barrier; the next one writes the other buffer (par, the
+// running block's parity), since a wave may reach it before the other wave has
+// read what this one brought.
 constexpr int kHalo = 8;
 struct QHalf {
   int hf, K;
@@ -344,11 +347,11 @@ __device__ __forceinline__ void qv_forward(const wide_rsrc_t (&rb)[6], const QV<
         norm_weights<LG, NP>(a, b, c, ln.pos0, W, renorm);
         line_step<NP>(xv, lv, a, b, c, ln.valid, hp);
         load(k, s + R);
-        if (XE && kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange(ub & 1, hp);
+        if (XE && kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange((b0 + ub) & 1, hp);
         emit(rows.line(s), rows.line(s + 1), rows.soff(s), hp, v[NM - 1]);
       }
       end(b0 + ub, rows.nb);
-      if (!XE && b0 + ub + 1 < rows.nb) exchange(ub & 1, hp);
+      if (!XE && b0 + ub + 1 < rows.nb) exchange((b0 + ub) & 1, hp);
     }
   }
 }
@@ -623,7 +626,7 @@ __device__ __forceinline__ void qv_adjoint(const wide_rsrc_t (&rb)[5], const wid
         }
         read_h(s + 2);
         q_adjoint_g<NP>(uv, dyv, ln.valid, a0, a1, a2, gv);
-        if (kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange(ub & 1, gv);
+        if (kk == kHalo - 1 && b0 + ub + 1 < rows.nb) exchange((b0 + ub) & 1, gv);
         q_adjoint_w<NP, LG>(w0, w1, w2, hv, gv, ln.pos0, W, renorm, rst, a0, a1, a2, dv);
         load(k, s + R);
         const int line = rows.line(s), so = rows.soff(s);

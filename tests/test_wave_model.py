@@ -58,6 +58,10 @@ def model(tmp_path_factory):
         return dict(zip(keys, ex.map(compile_one, keys)))
 
 
+def case_id(v):
+    return "x".join(map(str, v)) if isinstance(v, tuple) else str(v)[6:]
+
+
 def ptr(t):
     return ctypes.c_void_p(t.data_ptr())
 
@@ -93,6 +97,61 @@ def check_forward(model, case, dtype):
                                         ((1, 24, 120, 3, 0, 0, False), F32), ((1, 19, 113, 15, 7, 40, True), F32),
                                         ((1, 24, 250, 15, 0, 0, False), F32), ((1, 24, 240, 15, 0, 0, True), BF16),
                                         ((1, 17, 200, 15, 0, 0, False), BF16), ((1, 24, 120, 14, 0, 0, False), F32)],
-                         ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v)[6:])
+                         ids=case_id)
 def test_merge_order(model, case, dtype):
     check_forward(model, case, dtype)
+
+
+def check_backward(model, case, dtype, pair):
+    planes, H, W, mask, gh, gw, logits = case
+    inp, a, opt = inputs(case, dtype)
+    runs = []
+    for o in ORDERS:
+        got = [torch.full_like(inp[k], float("nan")) for k in ("x", "w", "lam", "u")]
+        sums = [torch.full(inp["x"].shape, float("nan")) for _ in range(2)]
+        st = model[dtype, logits].model_bwd(*[ptr(inp[k]) for k in ("dy", "x", "w", "lam", "u")],
+                                            *[ptr(t) for t in got + sums], ctypes.c_int64(planes), H, W, mask, gh,
+                                            gw, int(pair), (ctypes.c_int * 4)(*o))
+        assert st == 0
+        runs.append(got)
+    ref = O.scan_bwd(a["dy"], a["x"], a["w"], a["lam"], a["u"], mask, **opt)
+    for i, name in enumerate(("dx", "dw", "dlam", "du")):
+        e = normwise(runs[0][i], ref[i])
+        assert torch.isfinite(runs[0][i]).all() and e <= TOL[dtype], f"{case}: {name}: {e:.3e}"
+        for o, r in zip(ORDERS, runs):
+            assert torch.equal(runs[0][i], r[i]), f"{case}: {name}: the waves in the order {o} give another result"
+
+
+# rings of 4 to 16 rows on lines that two waves share; even and odd block counts
+SHARED = [((1, 104, 152, 15, 0, 0, False), F32), ((1, 112, 144, 15, 0, 0, True), F32),
+          ((1, 64, 240, 15, 17, 50, False), F32), ((1, 72, 66, 7, 0, 0, False), F32),
+          ((1, 40, 240, 15, 0, 0, True), BF16), ((1, 48, 250, 13, 0, 0, False), BF16),
+          ((1, 96, 168, 15, 0, 0, False), BF16), ((1, 130, 70, 15, 33, 0, True), BF16)]
+
+
+@pytest.mark.parametrize("case,dtype", SHARED, ids=case_id)
+def test_edge_exchange_forward(model, case, dtype):
+    check_forward(model, case, dtype)
+
+
+@pytest.mark.parametrize("case,dtype", SHARED, ids=case_id)
+def test_edge_exchange_backward(model, case, dtype):
+    check_backward(model, case, dtype, True)
+
+
+@pytest.mark.parametrize("W,dtype", [(72, F32), (116, F32), (240, F32), (240, BF16)], ids=str)
+def test_every_block_count(model, W, dtype):
+    """1 to 20 blocks of rows at each ring depth (16, 8 and 4 rows; 8 for bf16)."""
+    for nb in range(1, 21):
+        H = 8 * nb - nb % 3
+        if (H + 1) * (W + 2) * 4 <= 160 * 1024:
+            check_forward(model, (1, H, W, 3, 0, 0, False), dtype)
+
+
+@pytest.mark.parametrize("case,dtype", [((5, 14, 14, 15, 0, 0, True), BF16), ((3, 20, 31, 15, 6, 9, False), F32),
+                                        ((2, 45, 33, 11, 0, 0, False), BF16), ((1, 64, 60, 15, 0, 0, True), F32)],
+                         ids=case_id)
+def test_one_wave_a_direction(model, case, dtype):
+    """The quad kernels: the directions of an axis meet at the merge only."""
+    check_forward(model, case, dtype)
+    check_backward(model, case, dtype, False)
