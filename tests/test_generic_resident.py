@@ -115,3 +115,30 @@ def test_generic_forward_one_sum(case, dtype):
                 e = normwise(y, O.scan_fwd(*[np64(t) for t in args], mask, lam_per_dir=pd, **opt))
                 assert torch.isfinite(y).all() and e <= TOL[dtype], f"{e:.3e}"
             assert torch.equal(y, first)
+
+
+# more planes than compute units on lines of two waves with rings of four and
+# eight rows (an odd and an even count of row blocks): workgroups start warm and
+# at different times, which a single plane never shows
+MANY = [((300, 104, 152, 15, 0, 0, False), torch.float32), ((300, 136, 144, 15, 0, 0, True), torch.float32),
+        ((300, 64, 240, 15, 23, 0, False), torch.float32), ((300, 40, 240, 15, 0, 0, True), torch.bfloat16)]
+
+
+@pytest.mark.parametrize("case,dtype", MANY, ids=lambda v: "x".join(map(str, v)) if isinstance(v, tuple) else str(v)[6:])
+def test_generic_resident_many_planes(case, dtype):
+    planes, H, W, mask, gh, gw, logits = case
+    print(f"[many planes] {case} {dtype}", flush=True)
+    inp = synth.random_general((1, planes, H, W), 4, device=DEV, seed=H * 300 + W, dtype=dtype)
+    args = [inp[k] for k in ("x", "w", "lam", "u")]
+    opt = dict(group_h=gh, group_w=gw, logits=logits)
+    run = lambda: (ops.gspn_scan_fwd(*args, mask, **opt),) + tuple(ops.gspn_scan_bwd(inp["dy"], *args, mask, **opt))
+    first = run()
+    torch.cuda.synchronize()
+    a = [np64(t) for t in args]
+    ref = (O.scan_fwd(*a, mask, **opt),) + tuple(O.scan_bwd(np64(inp["dy"]), *a, mask, **opt))
+    for name, g, r in zip(("y", "dx", "dw", "dlam", "du"), first, ref):
+        e = normwise(g, r)
+        assert torch.isfinite(g).all() and e <= TOL[dtype], f"{name}: {e:.3e}"
+    for _ in range(5):
+        for name, g, h in zip(("y", "dx", "dw", "dlam", "du"), first, run()):
+            assert torch.equal(g, h), name
