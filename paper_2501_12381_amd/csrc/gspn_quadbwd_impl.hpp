@@ -44,6 +44,12 @@ struct QBwdParams {
   // finishes, written by the one before it (null: this axis alone)
   float* hsum;
   float* gsum;
+  // the maps from `n` elements on (npc stays the stride between them)
+  template <typename T>
+  void skip(int64_t n) {
+    dy = (const T*)dy + n; x = (const T*)x + n; lam = (const T*)lam + n; w = (const T*)w + n; u = (const T*)u + n;
+    dx = (T*)dx + n; dw = (T*)dw + n; dlam = (T*)dlam + n; du = (T*)du + n;
+  }
 };
 
 // TV: vectors of a row in the registers of a horizontal wave (narrow planes
@@ -377,14 +383,7 @@ inline bool quad_bwd_size_fits(int H, int W) {
 
 template <typename T, int NPV, int NPH, int VL, bool LG, int TV = QVecs<NPH>::TV>
 hipError_t launch_quad_bwd_k(const QBwdParams& p, int lds, hipStream_t st) {
-  auto kern = quad_bwd_kernel<T, NPV, NPH, VL, TV, LG>;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-  }
-  const int64_t ppw = 64 >> p.segsh;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((p.planes + ppw - 1) / ppw)), dim3(256), lds, st, p);
-  return hipGetLastError();
+  return quad_launch<T>(quad_bwd_kernel<T, NPV, NPH, VL, TV, LG>, p, 64 >> p.segsh, lds, st);
 }
 
 template <typename T, bool LG>

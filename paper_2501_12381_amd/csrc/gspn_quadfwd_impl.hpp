@@ -36,6 +36,12 @@ struct QFwdParams {
   int renorm;
   int lam_pd, u_pd;  // per-direction maps (u_pd: unmerged outputs only)
   int split;         // duo: lines of at least 32 positions go to two waves
+  // the maps from `n` elements on (npc stays the stride between them)
+  template <typename T>
+  void skip(int64_t n) {
+    x = (const T*)x + n; lam = (const T*)lam + n; w = (const T*)w + n; u = (const T*)u + n;
+    y = (T*)y + n;
+  }
 };
 
 // TV: vectors of a row in the registers of a horizontal wave (narrow planes
@@ -299,6 +305,26 @@ inline int64_t quad_lds(const QConfig& c, int H, int arrays) {
   return (int64_t)(64 >> c.segsh) * arrays * (H + 1) * c.P * 4;
 }
 constexpr int kQuadMaxLds = 160 * 1024;
+
+// Launches `kern` (256 threads, `ppw` planes a workgroup) over every plane.  A
+// launch's threads are counted in 32 bits, which four waves a plane reach at
+// 16.8 million planes: more go in several launches.
+template <typename T, typename Q>
+hipError_t quad_launch(void (*kern)(Q), Q p, int ppw, int lds, hipStream_t st) {
+  constexpr int64_t most = 0xffffffffll / 256;  // workgroups
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+    if (e != hipSuccess) return e;
+  }
+  for (int64_t left = p.planes;;) {
+    p.planes = left < most * ppw ? left : most * ppw;
+    hipLaunchKernelGGL(kern, dim3((unsigned)((p.planes + ppw - 1) / ppw)), dim3(256), lds, st, p);
+    const hipError_t e = hipGetLastError();
+    left -= p.planes;
+    if (e != hipSuccess || left == 0) return e;
+    p.template skip<T>(p.planes * p.H * p.W);
+  }
+}
 constexpr int kDuoXbuf = 2 * 2 * 2 * kHalo * 4;  // exchange buffers of the duo kernel
 
 inline bool quad_fwd_size_fits(int H, int W, bool unmerged) {
@@ -308,24 +334,11 @@ inline bool quad_fwd_size_fits(int H, int W, bool unmerged) {
 
 template <typename T, int NPV, int NPH, int VL, bool LG, bool PD, int TV = QVecs<NPH>::TV>
 hipError_t launch_quad_fwd_k(const QFwdParams& p, int lds, hipStream_t st) {
-  auto kern = quad_fwd_kernel<T, NPV, NPH, VL, TV, LG, PD>;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-  }
-  const int64_t ppw = 64 >> p.segsh;
-  hipLaunchKernelGGL(kern, dim3((unsigned)((p.planes + ppw - 1) / ppw)), dim3(256), lds, st, p);
-  return hipGetLastError();
+  return quad_launch<T>(quad_fwd_kernel<T, NPV, NPH, VL, TV, LG, PD>, p, 64 >> p.segsh, lds, st);
 }
 template <typename T, int NPV, int NPH, bool LG, bool LX>
 hipError_t launch_duo_fwd_k(const QFwdParams& p, int lds, hipStream_t st) {
-  auto kern = duo_fwd_kernel<T, NPV, NPH, 16 / (int)sizeof(T), LG, LX>;
-  if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.planes), dim3(256), lds, st, p);
-  return hipGetLastError();
+  return quad_launch<T>(duo_fwd_kernel<T, NPV, NPH, 16 / (int)sizeof(T), LG, LX>, p, 1, lds, st);
 }
 
 // positions a lane of a wave that holds half a line and the halo of the other half

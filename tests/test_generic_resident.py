@@ -142,3 +142,13 @@ def test_generic_resident_many_planes(case, dtype):
     for _ in range(5):
         for name, g, h in zip(("y", "dx", "dw", "dlam", "du"), first, run()):
             assert torch.equal(g, h), name
+
+
+def test_generic_resident_more_planes_than_one_launch():
+    """67.2 million planes of one pixel: more than one launch's threads (2^32) cover."""
+    n = 67_200_000
+    x, lam, u, dy = (torch.rand((1, n, 1, 1), device=DEV) for _ in range(4))
+    w = torch.zeros((1, 3, 1, n, 1, 1), device=DEV)
+    for got, ref in zip((ops.gspn_scan_fwd(x, w, lam, u, 1),) + tuple(ops.gspn_scan_bwd(dy, x, w, lam, u, 1)),
+                        (u * (lam * x), lam * (u * dy), w, x * (u * dy), dy * (lam * x))):
+        assert torch.equal(got, ref)  # one product of two at a time, each rounded once

@@ -155,3 +155,13 @@ def test_one_wave_a_direction(model, case, dtype):
     """The quad kernels: the directions of an axis meet at the merge only."""
     check_forward(model, case, dtype)
     check_backward(model, case, dtype, False)
+
+
+# (forward or backward, H, W, planes a workgroup, launches for 40 million planes)
+@pytest.mark.parametrize("which,H,W,ppw,n", [(0, 1, 1, 4, 1), (0, 16, 2, 2, 2), (0, 33, 1, 1, 3), (0, 1, 66, 1, 3),
+                                             (1, 3, 5, 4, 1), (1, 2, 20, 2, 2), (1, 40, 1, 1, 3)])
+def test_more_planes_than_one_launch(model, which, H, W, ppw, n):
+    """A launch's threads are counted in 32 bits; every plane gets a workgroup all the same."""
+    planes, groups = 40_000_001, ctypes.c_int64()
+    got = model[F32, False].model_launches(which, ctypes.c_int64(planes), H, W, ctypes.byref(groups))
+    assert (got, groups.value) == (n, -(-planes // ppw))

@@ -177,7 +177,7 @@ inline void run_block(int threads, size_t lds_bytes) {
 
 inline void launch(dim3 grid, dim3 block, size_t lds_bytes, const std::function<void()>& f) {
   grids.push_back((uint64_t)grid.x * block.x);
-  // the runtime counts a dimension's work items in 32 bits
+  // a dimension's work items are counted in 32 bits (the GPU runs fewer without an error)
   if (grids.back() > 0xffffffffull || grid.x == 0) {
     last_error = hipErrorInvalidConfiguration;
     return;

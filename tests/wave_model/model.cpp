@@ -59,4 +59,24 @@ int model_bwd(const void* dy, const void* x, const void* w, const void* lam, con
   return launch_pair_bwd<T, MODEL_LG>(p, nullptr);
 }
 
+// The launches of a forward (which 0) or backward (1) over so many planes,
+// recorded and not run: their number, -1 where one is too large; groups:
+// their workgroups in all.
+int model_launches(int which, int64_t planes, int H, int W, int64_t* groups) {
+  const int order[4] = {0, 1, 2, 3};
+  setup(order);
+  sim::dry = true;
+  ResidentFwdArgs f{};
+  ResidentBwdArgs b{};
+  f.planes = b.planes = planes;
+  f.H = b.H = H;
+  f.W = b.W = W;
+  f.mask = b.mask = 15;
+  const hipError_t e = which ? launch_quad_bwd<T, MODEL_LG>(quad_bwd_params(b), nullptr)
+                             : launch_quad_fwd<T, MODEL_LG>(quad_fwd_params(f), nullptr);
+  *groups = 0;
+  for (uint64_t g : sim::grids) *groups += (int64_t)(g / 256);
+  return e == hipSuccess ? (int)sim::grids.size() : -1;
+}
+
 }  // extern "C"
