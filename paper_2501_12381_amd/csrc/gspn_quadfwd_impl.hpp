@@ -44,8 +44,8 @@ struct QFwdParams {
   }
 };
 
-// TV: vectors of a row in the registers of a horizontal wave (narrow planes
-// need few, and more workgroups then share a compute unit)
+// TV: vectors of a row in the registers of a horizontal wave (fewer let more
+// workgroups share a compute unit)
 template <typename T, int NPV, int NPH, int VL, int TV, bool LG, bool PD>
 __global__ void __launch_bounds__(256, NPH > 1 ? 1 : (TV <= 4 ? 4 : 2)) quad_fwd_kernel(QFwdParams p) {
   constexpr int ES = (int)sizeof(T), VE = VL;
@@ -378,9 +378,16 @@ hipError_t launch_quad_fwd(QFwdParams p, hipStream_t st) {
       return c.nph == 1 ? launch_quad_fwd_k<T, 1, 1, 1, LG, false>(p, lds, st)
            : c.nph == 2 ? launch_quad_fwd_k<T, 1, 2, 1, LG, false>(p, lds, st)
                         : launch_quad_fwd_k<T, 1, 4, 1, LG, false>(p, lds, st);
+    // Rows longer than two vectors: four in a group, which lets four workgroups share
+    // a compute unit, not eight, which holds two (2048 planes, eight -> four: 8 x 64
+    // fp32 59 -> 37 us, bf16 48 -> 29; 48 x 48 fp32 77 -> 72, bf16 55 -> 44), but for fp32
+    // planes over 10 KB, whose rows' cache lines do not last until their second half
+    // is read (45 x 60 92 -> 99, 60 x 64 113 -> 126).
+    if constexpr (sizeof(T) == 4) {
+      if (p.H * p.W > 2560) return launch_quad_fwd_k<T, 1, 1, VL, LG, false, 8>(p, lds, st);
+    }
     return p.W <= 2 * VL ? launch_quad_fwd_k<T, 1, 1, VL, LG, false, 2>(p, lds, st)
-         : p.W <= 4 * VL ? launch_quad_fwd_k<T, 1, 1, VL, LG, false, 4>(p, lds, st)
-                         : launch_quad_fwd_k<T, 1, 1, VL, LG, false>(p, lds, st);
+                         : launch_quad_fwd_k<T, 1, 1, VL, LG, false, 4>(p, lds, st);
   }
   p.split = one + kDuoXbuf <= kQuadMaxLds;  // else the lines stay whole: the sum fills LDS to the last bytes
   // the second array costs no workgroup: two of them share a compute unit all
@@ -399,9 +406,12 @@ hipError_t launch_quad_fwd_pd(QFwdParams p, hipStream_t st) {
   if (!quad_config(p.H, p.W, &c)) return hipErrorInvalidValue;
   p.P = c.P;
   p.segsh = c.segsh;
-  if (c.npv == 1 && c.nph == 1 && p.W >= VL && p.W <= 4 * VL)
-    return p.W <= 2 * VL ? launch_quad_fwd_k<T, 1, 1, VL, LG, true, 2>(p, 0, st)
-                         : launch_quad_fwd_k<T, 1, 1, VL, LG, true, 4>(p, 0, st);
+  // planes of few rows leave most lanes of the horizontal waves idle, and more
+  // workgroups a compute unit count more than long loads (2048 planes fp32, eight
+  // vectors -> two: 8 x 64 53 -> 30 us, 16 x 32 34 -> 26; 32 x 40 50 -> 62)
+  if (c.npv == 1 && c.nph == 1 && p.W >= VL && (p.W <= 4 * VL || p.H <= 16))
+    return p.W <= 2 * VL || p.H <= 16 ? launch_quad_fwd_k<T, 1, 1, VL, LG, true, 2>(p, 0, st)
+                                      : launch_quad_fwd_k<T, 1, 1, VL, LG, true, 4>(p, 0, st);
   auto h = [&](auto npv) -> hipError_t {
     constexpr int V = decltype(npv)::value;
     switch (c.nph) {

@@ -22,7 +22,10 @@ CASES = [(5, 3, 3, 15, 0, 0, False), (9, 7, 7, 15, 0, 0, True), (6, 7, 4, 15, 3,
          (1, 112, 113, 15, 0, 0, True), (2, 113, 112, 14, 40, 0, False), (1, 128, 129, 15, 0, 0, False),
          (1, 129, 136, 15, 17, 50, True), (1, 40, 240, 15, 0, 0, True), (1, 241, 40, 5, 0, 0, False),
          (1, 20, 250, 15, 0, 0, True), (1, 250, 36, 10, 0, 0, False), (2, 150, 66, 3, 0, 0, True),
-         (2, 66, 150, 12, 0, 0, True), (1, 8, 256, 15, 0, 0, False), (1, 256, 8, 15, 100, 3, True)]
+         (2, 66, 150, 12, 0, 0, True), (1, 8, 256, 15, 0, 0, False), (1, 256, 8, 15, 100, 3, True),
+         # rows of more than two vectors: vectors in a group change at 16 rows and at 2560 pixels
+         (3, 16, 64, 15, 0, 0, False), (2, 17, 60, 15, 5, 0, True), (2, 40, 64, 15, 0, 0, True),
+         (2, 41, 63, 15, 0, 20, False)]
 
 
 def misalign(t):
@@ -61,7 +64,7 @@ def test_generic_resident(case, dtype, shifted):
 
 @pytest.mark.parametrize("pd", [(True, False, False), (False, True, True), (True, True, True), (False, False, True)],
                          ids=lambda p: "".join("LUY"[i] if f else "-" for i, f in enumerate(p)))
-@pytest.mark.parametrize("shape", [(7, 5), (13, 30), (40, 100), (70, 90)], ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("shape", [(7, 5), (13, 30), (16, 60), (17, 60), (40, 100), (70, 90)], ids=lambda s: f"{s[0]}x{s[1]}")
 def test_generic_resident_per_direction(shape, pd):
     """Per-direction maps on the generic kernels (three directions, both dtypes)."""
     H, W = shape
