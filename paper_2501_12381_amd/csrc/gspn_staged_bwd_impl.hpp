@@ -548,10 +548,18 @@ hipError_t resident_bwd_t(const ResidentBwdArgs& a) {
   }
   if (a.use_staged && p.vec && !pd && staged_bwd_size_supported<T>(a.H, a.W))
     return launch_staged_bwd_size<T>(p, a.H, st);
-  // the generic kernel where it is the faster one (merged maps, 2048 bf16 / 1024
-  // fp32 planes: 56 x 56 fp32 158 against 196 us, 64 x 64 bf16 215 against 232;
-  // 56 x 56 bf16 179 against 176, per-direction maps 40 against 37)
-  if (!pd && a.use_staged && (sizeof(T) == 4 || a.H == 64)) return quad_bwd(a);
+  // The generic kernel where it is the faster one.  fp32: with a horizontal direction
+  // and another one, once the directions' waves fill the SIMDs (1024); before that the
+  // per-wave kernel's shorter chain counts (per-wave against generic, us: 56 x 56, four
+  // directions, 1 / 128 / 256 / 512 / 2048 planes 22 / 29 / 40 / 78 / 390 against
+  // 27 / 31 / 37 / 73 / 326; 64 x 64 the horizontal pair 20 / 24 / 35 / 69 / 282 against
+  // 32 / 34 / 37 / 62 / 242; the vertical pair 138 against 138 at 2048).  bf16: 64 x 64
+  // in four directions from 512 planes on (256 / 512 / 2048 planes 26 / 61 / 231 against
+  // 30 / 58 / 226, logits 33 / 69 / 258 against 37 / 63 / 252; three directions 162 against
+  // 162, two 144 against 160 at 2048).
+  const bool quad = sizeof(T) == 4 ? n >= 2 && (a.mask & (DIR_L2R | DIR_R2L)) && a.planes * n >= 1024
+                                   : a.H == 64 && n == 4 && a.planes >= 512;
+  if (!pd && a.use_staged && quad) return quad_bwd(a);
   switch (a.H) {
     case 16: return launch_resident_bwd<T, 16>(p, st);
     case 28: return launch_resident_bwd<T, 28>(p, st);

@@ -155,3 +155,24 @@ def test_generic_resident_more_planes_than_one_launch():
     for got, ref in zip((ops.gspn_scan_fwd(x, w, lam, u, 1),) + tuple(ops.gspn_scan_bwd(dy, x, w, lam, u, 1)),
                         (u * (lam * x), lam * (u * dy), w, x * (u * dy), dy * (lam * x))):
         assert torch.equal(got, ref)  # one product of two at a time, each rounded once
+
+
+# both sides of the line between the per-wave and the generic backward of 56 x 56 and 64 x 64 planes
+@pytest.mark.parametrize("planes,S,mask,dtype", [(255, 56, 15, torch.float32), (256, 56, 15, torch.float32),
+                                                 (341, 64, 7, torch.float32), (342, 64, 7, torch.float32),
+                                                 (600, 56, 3, torch.float32), (1030, 64, 4, torch.float32),
+                                                 (511, 64, 15, torch.bfloat16), (512, 64, 15, torch.bfloat16)],
+                         ids=str)
+def test_backward_of_56_and_64(planes, S, mask, dtype):
+    n = bin(mask).count("1")
+    print(f"[56 and 64] {planes} {S} {mask} {dtype}", flush=True)
+    inp = synth.random_general((1, planes, S, S), n, device=DEV, seed=planes, dtype=dtype)
+    args = [inp[k] for k in ("dy", "x", "w", "lam", "u")]
+    got = ops.gspn_scan_bwd(*args, mask, logits=True)
+    torch.cuda.synchronize()
+    for first in (0, planes - 2):  # the oracle takes the first and the last planes
+        cut = [t.narrow(-3, first, 2) for t in args]
+        ref = O.scan_bwd(*[np64(t) for t in cut], mask, logits=True)
+        for name, g, r in zip(("dx", "dw", "dlam", "du"), got, ref):
+            e = normwise(g.narrow(-3, first, 2), r)
+            assert e <= TOL[dtype], f"{name}: {e:.3e}"
