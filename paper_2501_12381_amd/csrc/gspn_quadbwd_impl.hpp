@@ -36,6 +36,7 @@ struct QBwdParams {
   void* du;
   int64_t npc, planes;
   int H, W, P, segsh;
+  int n;  // directions present
   int slot[4];
   int gh, gw;
   int renorm;
@@ -52,12 +53,13 @@ struct QBwdParams {
   }
 };
 
-// TV: vectors of a row in the registers of a horizontal wave (narrow planes
-// need few, and more workgroups then share a compute unit)
+// TV: vectors of a row in the registers of a horizontal wave (fewer let more
+// workgroups share a compute unit)
 template <typename T, int NPV, int NPH, int VL, int TV, bool LG>
-__global__ void __launch_bounds__(256, NPH > 1 ? 1 : (TV <= 2 ? 4 : (TV <= 4 ? 3 : 2))) quad_bwd_kernel(QBwdParams p) {
+__global__ void __launch_bounds__(256, NPH > 1 ? (TV == 4 ? 2 : 1) : (TV <= 2 && NPV < 4 ? 4 : (TV <= 4 ? 3 : 2)))
+quad_bwd_kernel(QBwdParams p) {
   constexpr int ES = (int)sizeof(T), VE = VL;
-  constexpr int RV = TV <= 2 ? kHalo : QRing<T, NPV>::RV;  // small planes have few rows
+  constexpr int RQ = QRing<T, NPV>::RV, RV = TV <= 2 && RQ > kHalo ? kHalo : RQ;  // small planes have few rows
   extern __shared__ float lds[];
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int ppw = 64 >> p.segsh;
@@ -70,7 +72,7 @@ __global__ void __launch_bounds__(256, NPH > 1 ? 1 : (TV <= 2 ? 4 : (TV <= 4 ? 3
   const int ARR = (p.H + 1) * p.P;
   const bool rev = wave & 1, hz = wave >= 2, rn = p.renorm != 0;
   const int slot = hz ? (rev ? p.slot[3] : p.slot[2]) : (rev ? p.slot[1] : p.slot[0]);
-  float* arr = lds + ((lane >> p.segsh) * 4 + wave) * ARR;
+  float* arr = lds + ((lane >> p.segsh) * p.n + (slot < 0 ? 0 : slot)) * ARR;
   const T* w0 = (const T*)p.w + (int64_t)(slot < 0 ? 0 : slot) * 3 * p.npc + gof;
   T* d0 = (T*)p.dw + (int64_t)(slot < 0 ? 0 : slot) * 3 * p.npc + gof;
   const wide_rsrc_t rw0 = q_rsrc(w0, bytes), rw1 = q_rsrc(w0 + p.npc, bytes), rw2 = q_rsrc(w0 + 2 * p.npc, bytes);
@@ -105,7 +107,7 @@ __global__ void __launch_bounds__(256, NPH > 1 ? 1 : (TV <= 2 ? 4 : (TV <= 4 ? 3
   constexpr int U = VE > 1 ? 2 : 4;
   const int64_t npc = p.npc;
   // a direction's value at an LDS offset of plane pl
-  auto at = [&](int pl, int d, int o) { return lds[(pl * 4 + d) * ARR + o]; };
+  auto at = [&](int pl, int d, int o) { return lds[(pl * p.n + p.slot[d]) * ARR + o]; };
   if (p.u_pd || p.y_pd) {
     q_flat<VE, 1>(
         g, threadIdx.x, 256, [](int, int) {},
@@ -393,33 +395,52 @@ hipError_t launch_quad_bwd(QBwdParams p, hipStream_t st) {
   if (!quad_config(p.H, p.W, &c)) return hipErrorInvalidValue;
   p.P = c.P;
   p.segsh = c.segsh;
-  const int64_t lds64 = quad_lds(c, p.H, 4);
-  if (lds64 > kQuadMaxLds) return hipErrorInvalidValue;
-  const int lds = (int)lds64;
+  if (quad_lds(c, p.H, 4) > kQuadMaxLds) return hipErrorInvalidValue;
+  // An array for each direction present, and the registers of the scans that run:
+  // both decide how many workgroups share a compute unit (2048 planes, four arrays and
+  // every scan's registers -> this: top-to-bottom alone 72 x 72 fp32 286 -> 157 us, bf16
+  // 297 -> 89, 200 x 4 fp32 367 -> 121; left-to-right alone 64 x 128 bf16 341 -> 186).
+  const int lds = (int)quad_lds(c, p.H, p.n);
+  const bool v = p.slot[0] >= 0 || p.slot[1] >= 0, h = p.slot[2] >= 0 || p.slot[3] >= 0;
+  const int npv = v ? c.npv : 1, nph = h ? c.nph : 1;
   if constexpr (VL > 4) {  // bf16 rows of 4 to 7: 8-byte vectors
-    if (p.W < VL && p.W >= 4 && c.nph == 1) return launch_quad_bwd_k<T, 1, 1, 4, LG, 2>(p, lds, st);
+    if (p.W < VL && p.W >= 4 && nph == 1) return launch_quad_bwd_k<T, 1, 1, 4, LG, 2>(p, lds, st);
   }
   if (p.W < VL) {
-    switch (c.nph) {
+    switch (nph) {
       case 1: return launch_quad_bwd_k<T, 1, 1, 1, LG>(p, lds, st);
       case 2: return launch_quad_bwd_k<T, 1, 2, 1, LG>(p, lds, st);
       default: return launch_quad_bwd_k<T, 1, 4, 1, LG>(p, lds, st);
     }
   }
+  // two vectors of a row also for planes of few rows, whose horizontal waves have most
+  // lanes idle: more workgroups count more than long loads (2048 planes, eight -> two:
+  // four directions 16 x 32 fp32 77 -> 60 us, 14 x 60 bf16 97 -> 62, 4 x 200 bf16 262 -> 146;
+  // left-to-right alone 16 x 32 fp32 59 -> 33)
+  if (p.W <= 2 * VL || p.H <= 16 || !h) {
+    if (nph == 1)
+      return npv == 1 ? launch_quad_bwd_k<T, 1, 1, VL, LG, 2>(p, lds, st)
+           : npv == 2 ? launch_quad_bwd_k<T, 2, 1, VL, LG, 2>(p, lds, st)
+                      : launch_quad_bwd_k<T, 4, 1, VL, LG, 2>(p, lds, st);
+  }
+  // a single horizontal direction runs on one wave of a workgroup: more of them, with
+  // shorter loads (2048 planes: 72 x 72 bf16 284 -> 188 us, 96 x 96 fp32 539 -> 452), but
+  // for fp32 planes of one row a lane over 10 KB (60 x 60 155 -> 190), as in the forward
+  if (p.n == 1 && nph == 1 && (sizeof(T) == 2 || p.H * p.W <= 2560))
+    return launch_quad_bwd_k<T, 1, 1, VL, LG, 4>(p, lds, st);
+  if (p.n == 1 && nph == 2) return launch_quad_bwd_k<T, 1, 2, VL, LG, 4>(p, lds, st);
   // four arrays of a plane with both sides over 128 do not fit
-  if (c.npv == 1 && c.nph == 1 && p.W <= 4 * VL)
-    return p.W <= 2 * VL ? launch_quad_bwd_k<T, 1, 1, VL, LG, 2>(p, lds, st)
-                         : launch_quad_bwd_k<T, 1, 1, VL, LG, 4>(p, lds, st);
-  if (c.npv == 1)
-    return c.nph == 1 ? launch_quad_bwd_k<T, 1, 1, VL, LG>(p, lds, st)
-         : c.nph == 2 ? launch_quad_bwd_k<T, 1, 2, VL, LG>(p, lds, st)
-                      : launch_quad_bwd_k<T, 1, 4, VL, LG>(p, lds, st);
-  if (c.npv == 2)
-    return c.nph == 1 ? launch_quad_bwd_k<T, 2, 1, VL, LG>(p, lds, st)
-         : c.nph == 2 ? launch_quad_bwd_k<T, 2, 2, VL, LG>(p, lds, st)
-                      : launch_quad_bwd_k<T, 2, 4, VL, LG>(p, lds, st);
-  return c.nph == 1 ? launch_quad_bwd_k<T, 4, 1, VL, LG>(p, lds, st)
-       : c.nph == 2 ? launch_quad_bwd_k<T, 4, 2, VL, LG>(p, lds, st) : hipErrorInvalidValue;
+  if (npv == 1 && nph == 1 && p.W <= 4 * VL) return launch_quad_bwd_k<T, 1, 1, VL, LG, 4>(p, lds, st);
+  if (npv == 1)
+    return nph == 1 ? launch_quad_bwd_k<T, 1, 1, VL, LG>(p, lds, st)
+         : nph == 2 ? launch_quad_bwd_k<T, 1, 2, VL, LG>(p, lds, st)
+                    : launch_quad_bwd_k<T, 1, 4, VL, LG>(p, lds, st);
+  if (npv == 2)
+    return nph == 1 ? launch_quad_bwd_k<T, 2, 1, VL, LG>(p, lds, st)
+         : nph == 2 ? launch_quad_bwd_k<T, 2, 2, VL, LG>(p, lds, st)
+                    : launch_quad_bwd_k<T, 2, 4, VL, LG>(p, lds, st);
+  return nph == 1 ? launch_quad_bwd_k<T, 4, 1, VL, LG>(p, lds, st)
+       : nph == 2 ? launch_quad_bwd_k<T, 4, 2, VL, LG>(p, lds, st) : hipErrorInvalidValue;
 }
 
 // Pair kernel: lines of at least 32 positions on both axes (two halves with
@@ -476,6 +497,7 @@ inline QBwdParams quad_bwd_params(const ResidentBwdArgs& a) {
   p.H = a.H; p.W = a.W;
   int n = 0;
   for (int d = 0; d < 4; ++d) p.slot[d] = (a.mask >> d) & 1 ? n++ : -1;
+  p.n = n;
   p.gh = (a.group_h > 0 && a.group_h < a.H) ? a.group_h : a.H;
   p.gw = (a.group_w > 0 && a.group_w < a.W) ? a.group_w : a.W;
   p.renorm = a.renorm;

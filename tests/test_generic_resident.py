@@ -25,7 +25,11 @@ CASES = [(5, 3, 3, 15, 0, 0, False), (9, 7, 7, 15, 0, 0, True), (6, 7, 4, 15, 3,
          (2, 66, 150, 12, 0, 0, True), (1, 8, 256, 15, 0, 0, False), (1, 256, 8, 15, 100, 3, True),
          # rows of more than two vectors: vectors in a group change at 16 rows and at 2560 pixels
          (3, 16, 64, 15, 0, 0, False), (2, 17, 60, 15, 5, 0, True), (2, 40, 64, 15, 0, 0, True),
-         (2, 41, 63, 15, 0, 20, False)]
+         (2, 41, 63, 15, 0, 20, False),
+         # one axis or one direction: arrays and registers of those alone
+         (2, 16, 70, 1, 0, 0, True), (2, 100, 60, 2, 9, 0, False), (2, 70, 16, 4, 0, 0, False),
+         (2, 60, 100, 8, 0, 30, True), (3, 30, 50, 8, 0, 0, False), (2, 14, 130, 5, 0, 0, True),
+         (3, 12, 200, 15, 5, 0, False), (5, 9, 11, 4, 0, 0, False)]
 
 
 def misalign(t):

@@ -149,7 +149,9 @@ def test_every_block_count(model, W, dtype):
 
 
 @pytest.mark.parametrize("case,dtype", [((5, 14, 14, 15, 0, 0, True), BF16), ((3, 20, 31, 15, 6, 9, False), F32),
-                                        ((2, 45, 33, 11, 0, 0, False), BF16), ((1, 64, 60, 15, 0, 0, True), F32)],
+                                        ((2, 45, 33, 11, 0, 0, False), BF16), ((1, 64, 60, 15, 0, 0, True), F32),
+                                        ((1, 41, 63, 15, 0, 0, False), F32), ((2, 16, 60, 8, 0, 9, True), BF16),
+                                        ((2, 10, 60, 1, 4, 0, False), F32), ((3, 30, 50, 4, 0, 0, False), BF16)],
                          ids=case_id)
 def test_one_wave_a_direction(model, case, dtype):
     """The quad kernels: the directions of an axis meet at the merge only."""
