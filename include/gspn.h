@@ -138,7 +138,9 @@ enum {
  * 32, 56 or 64); GSPN_FLAG_Y_PER_DIR alone also by the two-pass family.  AUTO
  * picks among those, and beyond the forced resident families' sizes among
  * generic resident kernels that take any alignment: unmerged outputs of any
- * plane up to 256 x 256, and the backward of planes whose states fit on chip
+ * plane up to 256 x 256 (many planes of over 128 rows and at least 64 KB run on
+ * the two-pass family, which takes a workspace; element-aligned ones do not),
+ * and the backward of planes whose states fit on chip
  * (per-direction maps: four fp32 arrays of the plane; else two, one axis at a
  * time, the other axis's sums through the workspace). */
 enum {

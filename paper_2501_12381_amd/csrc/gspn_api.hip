@@ -177,16 +177,38 @@ bool two_pass_fits(const Problem& p, int dtype, bool backward) {
 }
 
 // AUTO only: the generic resident kernels beyond the sizes of the forced
-// resident families.  Quad: unmerged outputs of any plane up to 256 x 256
-// (forward), four states a plane in LDS (backward); pair: the backward of
+// resident families.  Quad: unmerged outputs of any plane up to 256 x 256 but
+// many large ones (forward), four states a plane in LDS (backward); pair: the backward of
 // planes whose states fit one axis at a time.
 constexpr int kAlgoQuad = 100, kAlgoPair = 101;
+
+// Unmerged outputs that the quad kernel could take and the two-pass family does
+// sooner.  With lines of over 128 rows a compute unit holds one of its workgroups, so
+// more than 256 planes need another round, and planes of 64 KB and more keep the
+// two-pass kernels' compute units busy (300 planes, quad against two-pass, us: 256 x 256
+// fp32 939 against 594, bf16 429 / 298, 160 x 160 fp32 332 / 248; below the line 160 x 160
+// bf16 184 / 213, 128 x 256 fp32 275 / 292).  Within one round the two-pass kernels are
+// ahead from about 100 planes on where half of the quad kernel's waves idle (the
+// horizontal pair, 100 planes 256 x 256 bf16 119 / 99, 160 x 160 fp32 102 / 91; 24 planes 85 / 84),
+// and for fp32 planes of 128 KB, with logits 192 KB (100 planes 192 x 192 174 / 156, 256 planes
+// 256 x 256 688 / 455, with logits 670 / 505; 100 planes 160 x 160 111 / 120, with logits 192 x
+// 192 185 / 189).
+// Their column state has to fit the scratch of gspn_scan_fwd_noalloc.
+bool unmerged_two_pass(const Problem& p, int dtype) {
+  const int64_t bytes = p.H * p.W * (int64_t)esize(dtype);
+  if (p.H <= 128 || bytes < 64 * 1024 || p.planes <= 96) return false;
+  if (p.planes <= 256 && (p.mask & (DIR_T2B | DIR_B2T)) &&
+      (dtype != GSPN_F32 || bytes < (p.logits() ? 192 : 128) * 1024))
+    return false;
+  return p.planes * p.H * 16 <= (int64_t)GSPN_NOALLOC_SCRATCH_BYTES && two_pass_fits(p, dtype, false);
+}
 
 int choose_algo(const Problem& p, int dtype, int algo, bool backward) {
   if (algo == GSPN_ALGO_STREAM) return GSPN_ALGO_STREAM;
   if (algo == GSPN_ALGO_RESIDENT || algo == GSPN_ALGO_RESIDENT_GENERIC)
     return resident_fits(p, backward) ? algo : -1;
   if (algo == GSPN_ALGO_TWO_PASS) return two_pass_fits(p, dtype, backward) ? algo : -1;
+  if (!backward && p.y_pd() && unmerged_two_pass(p, dtype)) return GSPN_ALGO_TWO_PASS;
   if (resident_fits(p, backward)) return GSPN_ALGO_RESIDENT;
   const int H = (int)p.H, W = (int)p.W;
   if (backward) {
@@ -327,7 +349,8 @@ int gspn_scan_fwd(const void* x, const void* w, const void* lam, const void* u, 
       if ((uintptr_t)q % 16) {
         // a kept state must come from the two-pass kernels: no fallback then
         if (algo != GSPN_ALGO_AUTO || keep) return GSPN_ERR_ALIGN;
-        a = GSPN_ALGO_STREAM;  // its workspace is never larger than the two-pass one
+        // their workspaces are never larger than the two-pass one
+        a = p.y_pd() && gspn::quad_fwd_fits((int)H, (int)W, true) ? kAlgoQuad : GSPN_ALGO_STREAM;
         break;
       }
   }

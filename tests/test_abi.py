@@ -99,6 +99,20 @@ def test_workspace_sizes():
     # AUTO takes the two-pass kernels for planes that do not fit on chip
     big = L.gspn_scan_fwd_workspace_bytes(1, 2, 2048, 2048, 0xF, bf, algo=L.GSPN_ALGO_AUTO)
     assert big == 2 * (2 * 2048 * 2048 * 4) + 4 * 2 * 2048 * 4
+    # unmerged outputs: none on the generic resident kernels; the column state on the
+    # two-pass family: over 128 rows, from 64 KB on, for more than 256 planes, or more
+    # than 96 with horizontal directions alone or fp32 weights from 128 KB on
+    Y, LG = L.GSPN_FLAG_Y_PER_DIR, L.GSPN_FLAG_W_LOGITS
+    for planes, H, W, dt, mask, flags, two in (
+            (256, 136, 128, f32, 15, Y, False), (257, 136, 128, f32, 15, Y, True), (257, 128, 256, f32, 15, Y, False),
+            (257, 136, 120, f32, 15, Y, False), (257, 136, 128, bf, 15, Y, False), (257, 136, 248, bf, 15, Y, True),
+            (257, 136, 130, f32, 15, Y, False), (40000, 136, 128, f32, 15, Y, False),
+            (97, 136, 128, f32, 12, Y, True), (97, 136, 248, bf, 8, Y | LG, True), (96, 136, 128, f32, 12, Y, False),
+            (97, 136, 244, f32, 15, Y, True), (97, 136, 244, f32, 15, Y | LG, False),
+            (97, 200, 248, f32, 15, Y | LG, True), (97, 256, 256, bf, 15, Y, False),
+            (97, 136, 240, f32, 15, Y, False)):
+        got = L.gspn_scan_fwd_workspace_bytes(1, planes, H, W, mask, dt, flags=flags)
+        assert got == (-(-planes * H * 16 // 256) * 256 if two else 0), (planes, H, W, dt, mask, flags)
     # invalid problems report 0
     assert L.gspn_scan_fwd_workspace_bytes(2, 3, 5, 7, 0, f32, algo=S) == 0
     assert L.gspn_scan_fwd_workspace_bytes(2, 3, 5, 7, 1, 7, algo=S) == 0

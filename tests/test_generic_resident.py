@@ -180,3 +180,23 @@ def test_backward_of_56_and_64(planes, S, mask, dtype):
         for name, g, r in zip(("dx", "dw", "dlam", "du"), got, ref):
             e = normwise(g.narrow(-3, first, 2), r)
             assert e <= TOL[dtype], f"{name}: {e:.3e}"
+
+
+# unmerged outputs on both sides of the line between the quad kernel and the two-pass family
+@pytest.mark.parametrize("planes,H,W,dtype,mask", [(256, 136, 128, torch.float32, 15), (257, 136, 128, torch.float32, 15),
+                                                   (257, 136, 124, torch.float32, 13), (257, 160, 208, torch.bfloat16, 15),
+                                                   (300, 129, 256, torch.bfloat16, 3), (300, 128, 256, torch.float32, 12),
+                                                   (97, 136, 248, torch.bfloat16, 12), (100, 136, 244, torch.float32, 7)],
+                         ids=str)
+def test_unmerged_outputs_many_planes(planes, H, W, dtype, mask):
+    n = bin(mask).count("1")
+    print(f"[unmerged] {planes} {H} {W} {dtype} {mask}", flush=True)
+    inp = synth.random_general((1, planes, H, W), n, device=DEV, seed=H + W, dtype=dtype)
+    args = [inp[k] for k in ("x", "w", "lam", "u")]
+    for shift in (False, True):
+        y = ops.gspn_scan_fwd(*([misalign(t) for t in args] if shift else args), mask, y_per_dir=True)
+        torch.cuda.synchronize()
+        for first in (0, planes - 2):  # the oracle takes the first and the last planes
+            ref = O.scan_fwd(*[np64(t.narrow(-3, first, 2)) for t in args], mask, y_per_dir=True)
+            e = normwise(y.narrow(-3, first, 2), ref)
+            assert e <= TOL[dtype], f"shifted {shift}: {e:.3e}"
