@@ -92,6 +92,12 @@ def _check(x, w, lam, u, mask, lam_per_dir: bool, u_per_dir: bool):
     return n
 
 
+def _check_workspace(workspace, dev) -> None:
+    """A caller's workspace that is large enough to be used: the kernels write it as one run of bytes."""
+    if workspace.device != dev or not workspace.is_contiguous():
+        raise ValueError(f"workspace must be a contiguous tensor on {dev} (scan_workspace)")
+
+
 def _launch(fn, where: str, ptrs, sizes, flags: int, algo: int, workspace, dev) -> None:
     """Call the library's `fn` on the current stream of `dev`.
 
@@ -140,8 +146,8 @@ def gspn_scan_fwd(x, w, lam, u, mask: int, *, algo: int = L.GSPN_ALGO_AUTO, y=No
     yshape = _shape(x.shape, y_per_dir, n)
     if y is None:
         y = x.new_empty(yshape) if type(x) is torch.Tensor else torch.empty(yshape, dtype=x.dtype, device=dev)
-    elif y.shape != yshape or y.dtype != x.dtype or not y.is_contiguous():
-        raise ValueError(f"y must be a contiguous {x.dtype} tensor of shape {yshape}")
+    elif y.shape != yshape or y.dtype != x.dtype or y.device != dev or not y.is_contiguous():
+        raise ValueError(f"y must be a contiguous {x.dtype} tensor of shape {yshape} on {dev}")
     flags = _flags(logits, renorm, lam_per_dir, u_per_dir, y_per_dir, save_state)
     sizes = (*x.shape, mask, dt, group_h, group_w)
     need = _fwd_bytes(*sizes, flags, algo)
@@ -149,6 +155,8 @@ def gspn_scan_fwd(x, w, lam, u, mask: int, *, algo: int = L.GSPN_ALGO_AUTO, y=No
         if save_state:
             raise ValueError(f"the workspace holds {workspace.numel()} bytes, the forward needs {need}")
         workspace = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
+    elif need:
+        _check_workspace(workspace, dev)
     _launch(L.load().gspn_scan_fwd, "gspn_scan_fwd",
             (x.data_ptr(), w.data_ptr(), lam.data_ptr(), u.data_ptr(), y.data_ptr()), sizes, flags, algo,
             workspace, dev)
@@ -186,6 +194,8 @@ def gspn_scan_bwd(dy, x, w, lam, u, mask: int, *, algo: int = L.GSPN_ALGO_AUTO, 
         if save_state:
             raise ValueError(f"the workspace holds {workspace.numel()} bytes, the backward needs {need}")
         workspace = torch.empty(need, dtype=torch.uint8, device=dev) if need else None
+    elif need:
+        _check_workspace(workspace, dev)
     _launch(L.load().gspn_scan_bwd, "gspn_scan_bwd",
             (dy.data_ptr(), x.data_ptr(), w.data_ptr(), lam.data_ptr(), u.data_ptr(), dx.data_ptr(),
              dw.data_ptr(), dlam.data_ptr(), du.data_ptr()), sizes, flags, algo, workspace, dev)

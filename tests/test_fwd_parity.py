@@ -246,6 +246,22 @@ def test_errors_surface_as_exceptions():
     assert ei.value.status == 7
 
 
+def test_outputs_and_workspaces_off_the_device_rejected():
+    x = torch.zeros(1, 2, 300, 301, device=DEV)  # streaming: a workspace of one fp32 map (backward: three)
+    w = torch.zeros((2, 3) + tuple(x.shape), device=DEV)
+    with pytest.raises(ValueError, match="on cuda"):
+        ops.gspn_scan_fwd(x, w, x, x, 5, y=torch.empty(x.shape))
+    need = ops.scan_workspace(x, 5).numel()
+    for ws in (torch.empty(need, dtype=torch.uint8), torch.empty(1, dtype=torch.uint8, device=DEV).expand(need)):
+        with pytest.raises(ValueError, match="workspace"):
+            ops.gspn_scan_fwd(x, w, x, x, 5, workspace=ws)
+        with pytest.raises(ValueError, match="workspace"):
+            ops.gspn_scan_bwd(x, x, w, x, x, 5, workspace=ws)
+    # one too small to be used is replaced, wherever it is
+    y = ops.gspn_scan_fwd(x, w, x, x, 5, workspace=torch.empty(0, dtype=torch.uint8))
+    assert not y.any()
+
+
 def test_copy_calibration_kernel():
     src = torch.randint(0, 255, (3 * 1024 * 1024 + 37,), dtype=torch.uint8, device=DEV)
     dst = torch.zeros_like(src)
