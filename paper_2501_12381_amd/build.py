@@ -38,7 +38,7 @@ def hipcc() -> str:
 # units that take minutes to compile (one large kernel each, or many
 # instantiations); they start first so the parallel build is not left waiting
 # on one of them at the end
-SLOW_UNITS = ("gspn_widebwdlg_", "gspn_large_", "gspn_widebwd_", "gspn_resfwd_", "gspn_hadja_", "gspn_hadjb_",
+SLOW_UNITS = ("gspn_widebwdlg_", "gspn_large_", "gspn_widebwd_", "gspn_hadja_", "gspn_hadjb_",
               "gspn_widefwd_", "gspn_staged_")
 
 

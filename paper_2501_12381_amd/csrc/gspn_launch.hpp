@@ -155,8 +155,8 @@ inline hipError_t pair_bwd(const ResidentBwdArgs& a, float* hsum, float* gsum) {
 }
 bool pair_bwd_fits(int H, int W);
 
-// narr: accumulator arrays per plane of the forward (the directions present
-// for unmerged outputs, else 1)
+// Planes of the resident families as a caller can force them; narr: the directions
+// present for unmerged outputs of the forward, else 1.
 bool resident_fits(int H, int W, bool backward, int narr);
 
 // ---- two-pass family: planes too large for LDS -------------------------------

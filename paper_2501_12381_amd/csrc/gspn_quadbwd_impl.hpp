@@ -237,7 +237,7 @@ __global__ void __launch_bounds__(256, 1) pair_bwd_kernel(QBwdParams p, int fini
   const QPlanes g{p.H, p.W, p.P, 1, 6};
   const int bytes = HW * ES, fbytes = HW * 4;
   const int ARR = (p.H + (HZ ? 2 * kHalo : 0) + 1) * p.P;
-  const int L = HZ ? p.W : p.H, Pn = HZ ? p.H : p.W, grp = HZ ? p.gw : p.gh;
+  const int Pn = HZ ? p.H : p.W, grp = HZ ? p.gw : p.gh;
   const int K = ((Pn + 1) / 2 + NP - 1) / NP * NP;
   const int dir = wave >> 1;  // 0: top-to-bottom / left-to-right
   const bool rev = dir != 0, rn = p.renorm != 0;

@@ -199,7 +199,7 @@ __global__ void __launch_bounds__(256, 2) duo_fwd_kernel(QFwdParams p) {
   auto axis = [&](auto hzt) __attribute__((always_inline)) {
     constexpr bool HZ = decltype(hzt)::value;
     constexpr int NP = HZ ? NPH : NPV;
-    const int L = HZ ? p.W : p.H, Pn = HZ ? p.H : p.W, grp = HZ ? p.gw : p.gh;
+    const int Pn = HZ ? p.H : p.W, grp = HZ ? p.gw : p.gh;
     const bool split = Pn >= 32 && p.split;
     const int slot = p.slot[(HZ ? 2 : 0) + dir];
     const int nt = (p.W + VL - 1) / VL;  // vectors of a horizontal scan

@@ -220,8 +220,9 @@ hipError_t resident_fwd_t(const ResidentFwdArgs& a) {
   }
 }
 
-// narr: accumulator arrays per plane (the directions present, for unmerged
-// outputs, whose generic kernels need none)
+// Planes that a forced resident family takes (AUTO goes by quad_fwd_fits beyond).
+// narr: the directions present for unmerged outputs, else 1.  The kernels of unmerged
+// outputs hold no array; what a caller could force, and what was refused, stays so.
 inline bool resident_fwd_fits(int H, int W, int narr = 1) {
   using namespace resident_detail;
   if (H > kMaxLine || W > kMaxLine) return false;

@@ -153,7 +153,7 @@ hipError_t launch_vband(const VScanParams& p, const VBandGeom& g, bool lg, hipSt
   int s = -((E - p.H % E) % E);
   while (s < p.H) {
     bp.sb = s;
-    bp.se = g.nb == 1 ? p.H : std::min(p.H, s + g.rows);
+    bp.se = std::min(p.H, s + g.rows);
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * VBandCfg::NW), 0, st, bp);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -465,10 +465,9 @@ struct VBandGeom {
   int nb;    // bands
   int mid;   // lanes kept by an inner band; the first and last keep hb more (they have one halo)
 };
-inline VBandGeom vband_geom(int W, int rows) {
+inline VBandGeom vband_geom(int W, int rows) {  // rows wider than one band (vband_choose)
   using C = VBandCfg;
   const int lt = W / C::G, hb = rows / C::G;
-  if (lt <= C::SPAN) return {rows, hb, 1, lt};
   const int nb = (lt - 2 * hb + C::SPAN - 2 * hb - 1) / (C::SPAN - 2 * hb);
   return {rows, hb, nb, (lt - 2 * hb + nb - 1) / nb};
 }

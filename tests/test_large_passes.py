@@ -16,7 +16,7 @@ DEV = "cuda:0"
 # (planes, H, W, mask, group_h, group_w, logits)
 CASES = [(2, 9, 256, 15, 0, 0, False), (1, 8, 264, 15, 3, 0, True), (1, 7, 480, 3, 0, 0, False),
          (2, 17, 488, 6, 0, 0, True), (1, 33, 976, 15, 0, 0, False), (1, 16, 984, 15, 0, 100, True),
-         # column bands: one launch, its last row, one row more; one band and its neighbours
+         # column bands: one row, all but one of a launch's rows, all of them, one more; several launches
          (1, 1, 1024, 15, 0, 0, False), (1, 127, 1024, 15, 0, 0, True), (2, 128, 1288, 15, 50, 0, False),
          (1, 129, 1288, 15, 128, 0, True), (1, 257, 1024, 13, 0, 0, False), (1, 136, 2048, 14, 129, 7, True),
          # many planes: one workgroup a plane and direction
